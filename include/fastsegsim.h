@@ -273,7 +273,7 @@ fs_status fs_sort(uint64_t* keys, uint32_t* vals, int64_t pair_capacity, const i
  *              Depth and normal follow the same blend (and Top-K selection)
  *              as the features; FS_ERR_UNSUPPORTED with FS_TOPK_WEIGHT.
  *   counters   optional in/out, 4 uint64 added to: [0] list entries walked
- *              (over all 8x8 or 16x16 render blocks), [1] feature rows the
+ *              (over all 8x8 render blocks), [1] feature rows the
  *              blocks need (one per block and entry blended by any of its
  *              pixels), [2] blended (pixel, surfel) pairs, [3] blocks run
  *   keys       the sorted keys of fs_sort, read only for out_depth (else NULL)
