@@ -12,13 +12,20 @@
 // double-precision response decides acceptance, and entries after the
 // pixel's last blended position are skipped.
 //
-// Kernel 1 (per 8x8 block, one wave): the tile list is walked back to front
-// in batches.  Lanes = pixels recover T by division from the forward's final
-// transmittance and form the weights; lanes = channels form g . c_m (a wave
-// reduction per contribution) and accumulate w g into per-entry LDS rows;
-// lanes = pixels then run the scalar chain to dL/dL (9) and dL/do, reduced
-// over the wave per entry.  Per-entry results go to global memory with
-// atomics (float, so the sum order, hence the last bits, can vary).
+// Kernel 1 (per 8x8 block, four waves): the block's entries are walked back to
+// front in batches of 32.  All threads evaluate the (entry, pixel) pairs inside
+// the entries' pixel boxes; lanes = pixels recover T by division from the
+// forward's final transmittance and form the weights; groups of 16 threads own
+// an entry each and form g . c_m and the sum of w g over its pixels from the
+// block's upstream gradient, staged in LDS once; lanes = pixels run the suffix
+// sums; the groups then run the scalar chain to dL/dL (9) and dL/do over
+// their entries' accepted pixels.  Per-entry results go to global
+// memory with atomics (float, so the sum order, hence the last bits, can vary).
+// What bounds it is the serial chain of a long list's batches (five barriers
+// each), not the arithmetic, so every phase spreads a batch's pairs over as
+// many lanes as it can: one wave per block with a wave reduction per pair took
+// 2.75 ms for the 200k-surfel, 640x480, C = 48 full blend (16x16 tiles), this
+// form 0.28 ms.
 // Kernel 2 (per surfel): dL/dL -> dL/dadj(T) -> dL/dT -> centre, scales,
 // quaternion, summed over views, in double precision.
 #include "fs_internal.h"
@@ -35,13 +42,6 @@ template <>
 FS_DEV float to_f32<float>(float x) { return x; }
 template <>
 FS_DEV float to_f32<uint16_t>(uint16_t x) { return bf16_to_f32b(x); }
-
-// Butterfly sum over the wave (every lane gets the same bits).
-FS_DEV float wave_sum(float x) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x += __uint_as_float(lane_xor32(__float_as_uint(x), d));
-    return x;
-}
 
 // dL/dalpha of one (pixel, record) contribution -> dL/dL (9, rows of the
 // record's coefficient matrix times (1, dx, dy)) and dL/do, through alpha = o
@@ -72,174 +72,350 @@ __global__ void zero_f32_kernel(float* p, int64_t count) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) p[i] = 0.f;
 }
 
-template <int CPL, typename FT>
-__global__ void __launch_bounds__(64)
+// Position of the m-th set bit of x (m < popcount).
+FS_DEV int nth_bit(uint64_t x, int m) {
+    int p = 0;
+#pragma unroll
+    for (int sh = 32; sh >= 1; sh >>= 1) {
+        const int c = __popcll(x & ((1ull << sh) - 1ull));
+        if (m >= c) {
+            m -= c;
+            x >>= sh;
+            p += sh;
+        }
+    }
+    return p;
+}
+
+// Threads per entry and channels per thread of the feature phase: thread q of a
+// group owns channels q, q + 16, ..., so that a group's atomics to a gradient
+// row are contiguous.
+constexpr int kBwdThreads = 256;
+constexpr int kBwdGroup = 16;
+constexpr int kBwdGroups = kBwdThreads / kBwdGroup;
+constexpr int kBwdQueue = 512;   // entries queued by the filter (a power of two)
+constexpr uint32_t kBwdLong = 64;   // blocks with longer lists are started first
+
+// FILTER (tiles larger than a block): only entries whose pixel boxes meet the
+// block are walked, queued 256 list positions at a time.
+template <int CPT, typename FT, bool FILTER>
+struct BwdShared {
+    static constexpr int kRow = kBwdGroup * CPT + (kBwdGroup * CPT % 64 == 0 ? 16 : 0);   // spread over the banks
+    FsRecord rec[BG];
+    uint32_t recid[BG];
+    uint32_t sidx[BG];
+    float g[64][kRow];             // upstream gradient of the block's pixels, zero past C and past the image
+    float a[BG][64];               // alpha per accepted (entry, pixel)
+    float w[BG][64];               // weight
+    float d[BG][64];               // g . c, then dL/dalpha
+    uint32_t amask[64];            // per pixel: accepted entries of the batch
+    uint32_t emask[BG][2];         // per entry: accepted pixels
+    int last[64];
+    uint32_t qrid[FILTER ? kBwdQueue : 1];
+    uint32_t qpos[FILTER ? kBwdQueue : 1];
+    uint32_t qcount[kBwdThreads / 64];
+};
+
+template <int CPT, typename FT, bool FILTER>
+__global__ void __launch_bounds__(kBwdThreads)
 render_bwd_kernel(const FsRecord* __restrict__ records, const uint32_t* __restrict__ vals,
                   const uint32_t* __restrict__ ranges, const FT* __restrict__ feats, int C, int64_t n,
                   int64_t num_records, const fs_camera* __restrict__ cams, int num_views, int S, fs_opts o,
                   const float* __restrict__ out_T, const int32_t* __restrict__ out_last,
                   const float* __restrict__ grad_feat, float* __restrict__ grad_records,
                   float* __restrict__ grad_feats) {
-    constexpr int kChunk = 64 * CPL;
-    __shared__ FsRecord s_rec[BG];
-    __shared__ uint32_t s_recid[BG];
-    __shared__ float s_feat[BG][kChunk];
-    __shared__ float s_dfeat[BG][kChunk];
-    __shared__ float s_w[BG][64];
-    __shared__ float s_D[BG][64];
-    __shared__ float s_grec[BG][kGradFloats];
-
-    const int lane = threadIdx.x;
-    // block position (8x8 pixels inside a binning tile); the XCDs take one
-    // tile row of blocks each in turn (4.38 -> 3.99 ms on the 640x480
-    // full-blend backward)
-    const int sb = S / 8;
-    const int64_t b = xcd_remap_chunked(blockIdx.x, gridDim.x, block_row_chunk(cams, S));
-    const int64_t tile = b / (sb * sb);
-    const int sub = (int)(b % (sb * sb));
-    const int v = fs_view_of_tile(cams, num_views, tile);
-    const fs_camera& cam = cams[v];
-    const int tiles_x = (cam.width + S - 1) / S;
-    const int64_t local = tile - cam.tile_offset;
-    const int wx0 = (int)(local % tiles_x) * S + (sub % sb) * 8;
-    const int wy0 = (int)(local / tiles_x) * S + (sub / sb) * 8;
-    if (wx0 >= cam.width || wy0 >= cam.height) return;
-    const int px = wx0 + (lane & 7), py = wy0 + (lane >> 3);
+    constexpr int NT = kBwdThreads, NW = NT / 64;
+    constexpr int kQ = FS_RECORD_BYTES / 16;
+    constexpr int kRounds = BG / kBwdGroups;
+    static_assert(BG * kQ <= NT, "one record float4 per thread");
+    static_assert(2 * BG + NT <= kBwdQueue, "a refill fits the queue beside the batch in work and the next");
+    __shared__ BwdShared<CPT, FT, FILTER> sm;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // grid row 0 (dispatched first) takes the blocks with long lists, row 1 the
+    // others; the XCDs take one tile row of blocks each in turn
+    const bool second = blockIdx.y != 0;
+    const int64_t block = xcd_remap_chunked(blockIdx.x, gridDim.x, block_row_chunk(cams, S));
+    const BlockPos bp = locate_block(block, S, 8, cams, num_views);
+    if (!bp.valid) return;
+    const uint32_t start = ranges[2 * bp.tile], end = ranges[2 * bp.tile + 1];
+    if ((end - start > kBwdLong) == second || start >= end) return;
+    const fs_camera& cam = cams[bp.view];
+    const int px = bp.x0 + (lane & 7), py = bp.y0 + (lane >> 3);
     const bool inside = px < cam.width && py < cam.height;
     const int64_t pix = cam.pixel_offset + (int64_t)py * cam.width + px;
-    const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
     const int last = inside ? out_last[pix] : -1;
     // walk back from the block's last blended entry
-    int maxlast = last;
-    maxlast = __ockl_wfred_max_i32(maxlast);
+    const int maxlast = __ockl_wfred_max_i32(last);
     if (maxlast < (int)start) return;   // nothing was blended in this block
     // a last position from another frame's lists must not walk past this
     // tile's run into the next tile's entries
     const uint32_t top = min((uint32_t)maxlast + 1u, end);
-    if (top <= start) return;
-    double T = inside ? (double)out_T[pix] : 1.0;
-    float suffix = 0.f;                 // S: sum over later contributors of w (g . c)
+    const uint32_t len = top - start;   // entry i of the walk is list position top - 1 - i
+    double T = inside ? (double)out_T[pix] : 1.0;   // wave 0's walk
+    float suffix = 0.f;                             // S: sum over later contributors of w (g . c)
+    if (tid < 64) sm.last[tid] = last;
 
-    // upstream gradient of the block's pixels, lanes = channels
-    float G[64][CPL];
+    // records of the next batch are in flight while a batch is processed
+    float4 pre = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint32_t pre_rid = 0xffffffffu;
+    const int pe = tid / kQ, pq = tid - pe * kQ;    // record float4 of this thread: quarter pq of entry pe
+    auto fetch_record = [&](uint32_t rid) {
+        pre_rid = rid;
+        pre = make_float4(0.f, 0.f, 0.f, 0.f);
+        if ((int64_t)rid < num_records) pre = reinterpret_cast<const float4*>(records + rid)[pq];
+    };
+    auto val_at = [&](uint32_t i) { return i < len ? vals[top - 1u - i] : 0xffffffffu; };
+    uint32_t nxt_rid = 0xffffffffu;
+    uint32_t qh = 0, qt = 0, cp = 0;
+    uint32_t c_rid = 0xffffffffu, c_val = 0xffffffffu;
+    uint2 c_box = make_uint2(0u, 0u);
+    auto load_box = [&]() {
+        c_rid = c_val;
+        if ((int64_t)c_rid < num_records)
+            c_box = *reinterpret_cast<const uint2*>(&records[c_rid].x0);
+        else
+            c_rid = 0xffffffffu;
+    };
+    auto refill = [&]() {
+        const int x0 = (int16_t)(c_box.x & 0xffffu), x1 = (int16_t)(c_box.x >> 16);
+        const int y0 = (int16_t)(c_box.y & 0xffffu), y1 = (int16_t)(c_box.y >> 16);
+        const bool hit = c_rid != 0xffffffffu && x0 <= bp.x0 + 7 && x1 >= bp.x0 && y0 <= bp.y0 + 7 && y1 >= bp.y0 &&
+                         x0 <= x1 && y0 <= y1;
+        const uint64_t m = __ballot(hit);
+        if (lane == 0) sm.qcount[wave] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t at = qt;
 #pragma unroll
-    for (int p = 0; p < 64; ++p) {
-        const int qx = wx0 + (p & 7), qy = wy0 + (p >> 3);
-        const bool in = qx < cam.width && qy < cam.height;
-        const int64_t q = cam.pixel_offset + (int64_t)qy * cam.width + qx;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            const int ch = lane * CPL + c;
-            G[p][c] = (in && ch < C) ? grad_feat[q * C + ch] : 0.f;
+        for (int w = 0; w < NW; ++w) {
+            const uint32_t c = sm.qcount[w];
+            at += w < wave ? c : 0u;
+            qt += c;
         }
+        if (hit) {
+            const uint32_t i = (at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))) & (kBwdQueue - 1);
+            sm.qrid[i] = c_rid;
+            sm.qpos[i] = top - 1u - (cp + (uint32_t)tid);
+        }
+        cp += NT;
+        load_box();
+        c_val = val_at(cp + NT + (uint32_t)tid);
+        __syncthreads();
+    };
+    auto fetch_queued = [&](uint32_t h) {
+        fetch_record(pe < BG && h + (uint32_t)pe < qt ? sm.qrid[(h + pe) & (kBwdQueue - 1)] : 0xffffffffu);
+    };
+
+    if constexpr (FILTER) {
+        c_val = val_at((uint32_t)tid);
+        load_box();
+        c_val = val_at((uint32_t)(NT + tid));
+    } else {
+        fetch_record(pe < BG ? val_at((uint32_t)pe) : 0xffffffffu);
+        nxt_rid = pe < BG ? val_at((uint32_t)(BG + pe)) : 0xffffffffu;
     }
+    for (int t = tid; t < 64 * BwdShared<CPT, FT, FILTER>::kRow; t += NT) {
+        const int p = t / BwdShared<CPT, FT, FILTER>::kRow, c = t - p * BwdShared<CPT, FT, FILTER>::kRow;
+        const int qx = bp.x0 + (p & 7), qy = bp.y0 + (p >> 3);
+        const bool in = c < C && qx < cam.width && qy < cam.height;
+        sm.g[p][c] = in ? grad_feat[(cam.pixel_offset + (int64_t)qy * cam.width + qx) * C + c] : 0.f;
+    }
+    if constexpr (FILTER) {
+        while (qt < (uint32_t)BG && cp < len) refill();
+        fetch_queued(0);
+    }
+    const int q = tid % kBwdGroup, grp = tid / kBwdGroup;
 
-    const uint32_t nbatch = (top - start + BG - 1) / BG;
-    for (uint32_t bi = nbatch; bi-- > 0;) {
-        const uint32_t b0 = start + bi * BG;
-        const int nb = (int)(top - b0 < (uint32_t)BG ? top - b0 : (uint32_t)BG);
-        // 1. stage records
-        constexpr int kQ = FS_RECORD_BYTES / 16;
-        for (int t = lane; t < nb * kQ; t += 64) {
-            const int e = t / kQ, q = t - e * kQ;
-            uint32_t rid = vals[b0 + e];
-            float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
-            if ((int64_t)rid < num_records) {
-                v4 = reinterpret_cast<const float4*>(records + rid)[q];
-            } else {
+    for (uint32_t b0 = 0; FILTER ? qh != qt : b0 < len; b0 += BG) {
+        const uint32_t left = FILTER ? qt - qh : len - b0;
+        const int nb = (int)(left < (uint32_t)BG ? left : (uint32_t)BG);
+        // 1. stage the records; clear the batch's masks (all of it was last read
+        //    before the previous batch's final barrier)
+        if (pe < nb) {
+            uint32_t rid = pre_rid;
+            if ((int64_t)rid >= num_records) {   // never happens for a well-formed list
                 rid = 0u;
-                if (q == 4) v4.w = __int_as_float((int)0xbff00000);
-                if (q == 5) v4.z = __int_as_float(1);
+                if (pq == 4) pre.w = __int_as_float((int)0xbff00000);   // k2 = -1: never accepted
+                if (pq == 5) pre.z = __int_as_float(1);                 // empty box
             }
-            reinterpret_cast<float4*>(&s_rec[e])[q] = v4;
-            if (q == 0) s_recid[e] = rid;
-        }
-        for (int t = lane; t < BG * kGradFloats; t += 64) (&s_grec[0][0])[t] = 0.f;
-        for (int t = lane; t < BG * kChunk; t += 64) (&s_dfeat[0][0])[t] = 0.f;
-        __syncthreads();
-        // 2. weights, back to front (lanes = pixels)
-        uint32_t mask = 0u;
-        for (int e = nb - 1; e >= 0; --e) {
-            const FsRecord& r = s_rec[e];
-            if (r.x1 < wx0 || r.x0 > wx0 + 7 || r.y1 < wy0 || r.y0 > wy0 + 7) continue;
-            if ((int)(b0 + e) > last) continue;
-            const FsResp rs = fs_response(r, (double)(px - r.ax), (double)(py - r.ay));
-            if (rs.d2 <= r.k2 && fs_in_box(r, px, py)) {
-                const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
-                const float alpha = fminf(o.alpha_max, r.o * Gs);
-                T = T / (1.0 - (double)alpha);
-                s_w[e][lane] = (float)((double)alpha * T);
-                mask |= 1u << e;
+            reinterpret_cast<float4*>(&sm.rec[pe])[pq] = pre;
+            if (pq == 0) {
+                sm.recid[pe] = rid;
+                sm.sidx[pe] = rid % (uint32_t)n;
             }
         }
-        const uint32_t used = __ockl_wfred_or_u32(mask);
-        const uint64_t active_px = __ballot(mask != 0u);
-        // 3. feature rows of used entries
-        for (int t = lane; t < BG * kChunk; t += 64) {
-            const int e = t / kChunk, c = t - e * kChunk;
-            // channels >= C are zeroed: the wave-wide dot products read every lane
-            if ((used >> e) & 1u) s_feat[e][c] = c < C ? to_f32(feats[fs_surfel_of(s_recid[e], n) * C + c]) : 0.f;
-        }
+        if (tid < 64) sm.amask[tid] = 0u;
+        if (tid < 2 * BG) (&sm.emask[0][0])[tid] = 0u;
         __syncthreads();
-        // 4. lanes = channels: D = g . c per contribution, dL/dc += w g per entry
+        // list position of the batch's entry e
+        auto pos_of = [&](int e) -> int {
+            return FILTER ? (int)sm.qpos[(qh + e) & (kBwdQueue - 1)] : (int)(top - 1u - (b0 + (uint32_t)e));
+        };
+        // the feature rows of the group's entries: in flight during the
+        // response and weight phases
+        float f[kRounds][CPT];
 #pragma unroll
-        for (int p = 0; p < 64; ++p) {
-            if ((active_px >> p) & 1ull) {
-                uint32_t m = __builtin_amdgcn_readlane(mask, p);
-                while (m) {
-                    const int e = __builtin_ctz(m);
-                    m &= m - 1u;
-                    float part = 0.f;
+        for (int r = 0; r < kRounds; ++r) {
+            const int e = grp + r * kBwdGroups;
+            const FT* __restrict__ row = feats + (int64_t)(e < nb ? sm.sidx[e] : 0u) * C;
 #pragma unroll
-                    for (int c = 0; c < CPL; ++c) part = fmaf(G[p][c], s_feat[e][lane * CPL + c], part);
-                    const float D = wave_sum(part);
-                    if (lane == 0) s_D[e][p] = D;
-                    const float w = s_w[e][p];
+            for (int i = 0; i < CPT; ++i) {
+                const int c = q + i * kBwdGroup;
+                f[r][i] = e < nb && c < C ? to_f32(row[c]) : 0.f;
+            }
+        }
+        if constexpr (FILTER) {
+            while (qt - qh - nb < (uint32_t)BG && cp < len) refill();
+            fetch_queued(qh + nb);
+        } else if (b0 + BG < len) {
+            fetch_record(nxt_rid);
+            nxt_rid = pe < BG ? val_at(b0 + 2u * BG + (uint32_t)pe) : 0xffffffffu;
+        }
+        // 2. responses of the pairs inside the entries' boxes (numbered by a
+        //    prefix sum of the boxes' pixel counts, found by bisection)
+        {
+            int cnt_e = 0, packed = 0;
+            if (lane < nb) {
+                const FsRecord& r = sm.rec[lane];
+                const int xa = r.x0 > bp.x0 ? r.x0 : bp.x0;
+                const int ya = r.y0 > bp.y0 ? r.y0 : bp.y0;
+                int xb = r.x1 < bp.x0 + 7 ? r.x1 : bp.x0 + 7;
+                int yb = r.y1 < bp.y0 + 7 ? r.y1 : bp.y0 + 7;
+                xb = xb < cam.width - 1 ? xb : cam.width - 1;
+                yb = yb < cam.height - 1 ? yb : cam.height - 1;
+                if (xb >= xa && yb >= ya) {
+                    const int rw = xb - xa + 1, rh = yb - ya + 1;
+                    cnt_e = rw * rh;
+                    const int inv = (65536 + rw - 1) / rw;   // exact division of counts < 64 by rw <= 8
+                    packed = (xa - bp.x0) | ((ya - bp.y0) << 3) | (rw << 6) | (inv << 10);
+                }
+            }
+            const int Sc = __ockl_wfscan_add_i32(cnt_e, true);
+            const int M = __builtin_amdgcn_readlane(Sc, 31);
+            for (int base = wave * 64; base < M; base += NT) {   // uniform per wave: every lane shuffles
+                const int m = base + lane;
+                int e = 0;
 #pragma unroll
-                    for (int c = 0; c < CPL; ++c) s_dfeat[e][lane * CPL + c] += w * G[p][c];
+                for (int step = BG / 2; step >= 1; step >>= 1)
+                    if (__shfl(Sc, e + step - 1, 64) <= m) e += step;
+                const int prev = __shfl(Sc, e > 0 ? e - 1 : 0, 64);
+                const int pk = __shfl(packed, e, 64);
+                if (m < M) {
+                    const int local = m - (e > 0 ? prev : 0);
+                    const int rw = (pk >> 6) & 15, inv = pk >> 10;
+                    const int dy = (local * inv) >> 16, dx = local - dy * rw;
+                    const int lx = (pk & 7) + dx, ly = ((pk >> 3) & 7) + dy, p = ly * 8 + lx;
+                    const FsRecord& r = sm.rec[e];
+                    const FsResp rs = fs_response(r, (double)(bp.x0 + lx - r.ax), (double)(bp.y0 + ly - r.ay));
+                    if (rs.d2 <= r.k2 && pos_of(e) <= sm.last[p]) {
+                        const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
+                        sm.a[e][p] = fminf(o.alpha_max, r.o * Gs);
+                        atomicOr(&sm.amask[p], 1u << e);
+                        atomicOr(&sm.emask[e][p >> 5], 1u << (p & 31));
+                    }
                 }
             }
         }
         __syncthreads();
-        // 5. lanes = pixels: scalar chain back to front
-        for (int e = nb - 1; e >= 0; --e) {
-            if (!((used >> e) & 1u)) continue;
-            const bool mine = (mask >> e) & 1u;
-            float g[10];
-#pragma unroll
-            for (int k = 0; k < 10; ++k) g[k] = 0.f;
-            if (mine) {
-                const FsRecord& r = s_rec[e];
-                const double ddx = (double)(px - r.ax), ddy = (double)(py - r.ay);
-                const FsResp rs = fs_response(r, ddx, ddy);
-                const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
-                const float ag = r.o * Gs;
-                const bool clamped = ag > o.alpha_max;
-                const float alpha = clamped ? o.alpha_max : ag;
-                const float w = s_w[e][lane];
-                const float Tm = w / alpha;
-                const float D = s_D[e][lane];
-                const float dalpha = Tm * D - suffix / (1.f - alpha);
-                suffix = fmaf(w, D, suffix);
-                if (!clamped) blend_chain(r, rs, ddx, ddy, Gs, dalpha, g);
-            }
-#pragma unroll
-            for (int k = 0; k < 10; ++k) {
-                const float sum = wave_sum(g[k]);
-                if (lane == 0) s_grec[e][k] = sum;
+        // 3. weights, back to front (lanes = pixels)
+        if (wave == 0) {
+            uint32_t m = sm.amask[lane];
+            while (m != 0u) {
+                const int e = __builtin_ctz(m);
+                m &= m - 1u;
+                const double al = (double)sm.a[e][lane];
+                T = T / (1.0 - al);
+                sm.w[e][lane] = (float)(al * T);
             }
         }
         __syncthreads();
-        // 6. flush per-entry gradients
-        for (int t = lane; t < BG * kGradFloats; t += 64) {
-            const int e = t / kGradFloats, k = t - e * kGradFloats;
-            if (((used >> e) & 1u) && k < 10) atomicAdd(&grad_records[(int64_t)s_recid[e] * kGradFloats + k], s_grec[e][k]);
+        // 4. D = g . c per contribution, dL/dc = sum of w g per entry: a group
+        //    of 16 threads per entry, two of its pixels per step
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int e = grp + r * kBwdGroups;
+            uint64_t m = (uint64_t)sm.emask[e][0] | (uint64_t)sm.emask[e][1] << 32;
+            if (m == 0ull) continue;   // uniform inside the group
+            float acc[CPT];
+#pragma unroll
+            for (int i = 0; i < CPT; ++i) acc[i] = 0.f;
+            while (m != 0ull) {
+                const int p0 = __builtin_ctzll(m);
+                m &= m - 1ull;
+                const bool two = m != 0ull;
+                const int p1 = two ? __builtin_ctzll(m) : p0;
+                if (two) m &= m - 1ull;
+                const float w0 = sm.w[e][p0], w1 = two ? sm.w[e][p1] : 0.f;
+                float d0 = 0.f, d1 = 0.f;
+#pragma unroll
+                for (int i = 0; i < CPT; ++i) {
+                    const float g0 = sm.g[p0][q + i * kBwdGroup], g1 = sm.g[p1][q + i * kBwdGroup];
+                    d0 = fmaf(g0, f[r][i], d0);
+                    d1 = fmaf(g1, f[r][i], d1);
+                    acc[i] = fmaf(w0, g0, acc[i]);
+                    if (two) acc[i] = fmaf(w1, g1, acc[i]);
+                }
+#pragma unroll
+                for (int s = 1; s < kBwdGroup; s <<= 1) {
+                    d0 += __uint_as_float(lane_xor32(__float_as_uint(d0), s));
+                    d1 += __uint_as_float(lane_xor32(__float_as_uint(d1), s));
+                }
+                if (q == 0) {
+                    sm.d[e][p0] = d0;
+                    if (two) sm.d[e][p1] = d1;
+                }
+            }
+            float* __restrict__ dst = grad_feats + (int64_t)sm.sidx[e] * C;
+#pragma unroll
+            for (int i = 0; i < CPT; ++i)
+                if (q + i * kBwdGroup < C) atomicAdd(dst + q + i * kBwdGroup, acc[i]);
         }
-        for (int t = lane; t < BG * kChunk; t += 64) {
-            const int e = t / kChunk, c = t - e * kChunk;
-            if (((used >> e) & 1u) && c < C)
-                atomicAdd(&grad_feats[fs_surfel_of(s_recid[e], n) * C + c], s_dfeat[e][c]);
+        __syncthreads();
+        // 5. dL/dalpha, back to front (lanes = pixels)
+        if (wave == 0) {
+            uint32_t m = sm.amask[lane];
+            while (m != 0u) {
+                const int e = __builtin_ctz(m);
+                m &= m - 1u;
+                const float al = sm.a[e][lane], w = sm.w[e][lane], D = sm.d[e][lane];
+                sm.d[e][lane] = w / al * D - suffix / (1.f - al);
+                suffix = fmaf(w, D, suffix);
+            }
         }
+        __syncthreads();
+        // 6. the chain to the record's coefficients: the entry's group takes its
+        //    accepted pixels 16 at a time and sums over its lanes (a fixed order,
+        //    so only the order of the blocks' atomics varies from run to run)
+#pragma unroll 1
+        for (int e = grp; e < BG; e += kBwdGroups) {
+            const uint64_t m = (uint64_t)sm.emask[e][0] | (uint64_t)sm.emask[e][1] << 32;
+            const int np = __popcll(m);
+            if (np == 0) continue;   // uniform inside the group
+            const FsRecord& r = sm.rec[e];
+            float sum[10];
+#pragma unroll
+            for (int i = 0; i < 10; ++i) sum[i] = 0.f;
+            for (int k = q; k < np; k += kBwdGroup) {
+                const int p = nth_bit(m, k);
+                const double ddx = (double)(bp.x0 + (p & 7) - r.ax), ddy = (double)(bp.y0 + (p >> 3) - r.ay);
+                const FsResp rs = fs_response(r, ddx, ddy);
+                const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
+                if (r.o * Gs > o.alpha_max) continue;   // clamped: no gradient
+                float gg[10];
+                blend_chain(r, rs, ddx, ddy, Gs, sm.d[e][p], gg);
+#pragma unroll
+                for (int i = 0; i < 10; ++i) sum[i] += gg[i];
+            }
+#pragma unroll
+            for (int s = 1; s < kBwdGroup; s <<= 1)
+#pragma unroll
+                for (int i = 0; i < 10; ++i) sum[i] += __uint_as_float(lane_xor32(__float_as_uint(sum[i]), s));
+            float v = 0.f;   // component q of the sums
+#pragma unroll
+            for (int i = 0; i < 10; ++i) v = q == i ? sum[i] : v;
+            if (v != 0.f) atomicAdd(&grad_records[(int64_t)sm.recid[e] * kGradFloats + q], v);
+        }
+        qh += (uint32_t)nb;
         __syncthreads();
     }
 }
@@ -628,17 +804,37 @@ hipError_t launch_topk_grad(const FsRecord* records, const void* feats, int C, i
     return hipGetLastError();
 }
 
-template <int CPL, typename FT>
+template <int CPT, typename FT>
 hipError_t launch_bwd(const FsRecord* records, const uint32_t* vals, const uint32_t* ranges, const void* feats,
                       int C, int64_t n, const fs_camera* cams, int num_views, int64_t total_tiles, const fs_opts& o,
                       const float* out_T, const int32_t* out_last, const float* grad_feat, float* grad_records,
                       float* grad_feats, hipStream_t s) {
     const int sb = o.tile / 8;
     const int64_t blocks = total_tiles * sb * sb;
-    hipLaunchKernelGGL((render_bwd_kernel<CPL, FT>), dim3((unsigned)blocks), dim3(64), 0, s, records, vals, ranges,
-                       static_cast<const FT*>(feats), C, n, n * num_views, cams, num_views, o.tile, o, out_T,
-                       out_last, grad_feat, grad_records, grad_feats);
+    if (blocks >= (int64_t(1) << 32)) return hipErrorInvalidValue;
+    const auto kern = sb > 1 ? render_bwd_kernel<CPT, FT, true> : render_bwd_kernel<CPT, FT, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, 2), dim3(kBwdThreads), 0, s, records, vals, ranges,
+                       static_cast<const FT*>(feats), C, n, n * num_views, cams, num_views, o.tile, o, out_T, out_last,
+                       grad_feat, grad_records, grad_feats);
     return hipGetLastError();
+}
+
+template <typename FT>
+hipError_t launch_bwd_channels(const FsRecord* records, const uint32_t* vals, const uint32_t* ranges,
+                               const void* feats, int C, int64_t n, const fs_camera* cams, int num_views,
+                               int64_t total_tiles, const fs_opts& o, const float* out_T, const int32_t* out_last,
+                               const float* grad_feat, float* grad_records, float* grad_feats, hipStream_t s) {
+#define FS_BWD(CPT)                                                                                             \
+    return launch_bwd<CPT, FT>(records, vals, ranges, feats, C, n, cams, num_views, total_tiles, o, out_T, out_last, \
+                               grad_feat, grad_records, grad_feats, s)
+    // channels per thread of a 16-thread group: the row is padded to 16 CPT
+    if (C <= 16) FS_BWD(1);
+    if (C <= 32) FS_BWD(2);
+    if (C <= 48) FS_BWD(3);
+    if (C <= 64) FS_BWD(4);
+    if (C <= 128) FS_BWD(8);
+#undef FS_BWD
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -673,16 +869,12 @@ hipError_t fs_launch_render_backward(const float* means, const float* scales, co
                                               grad_records, grad_feats, ws, s)
                  : launch_topk_grad<float>(records, feats, C, n, cams, num_views, nblocks, o, grad_feat, grad_records,
                                            grad_feats, ws, s);
-    } else if (C <= 64)
-        e = bf16 ? launch_bwd<1, uint16_t>(records, vals, ranges, feats, C, n, cams, num_views, total_tiles, o, out_T,
-                                           out_last, grad_feat, grad_records, grad_feats, s)
-                 : launch_bwd<1, float>(records, vals, ranges, feats, C, n, cams, num_views, total_tiles, o, out_T,
-                                        out_last, grad_feat, grad_records, grad_feats, s);
-    else
-        e = bf16 ? launch_bwd<2, uint16_t>(records, vals, ranges, feats, C, n, cams, num_views, total_tiles, o, out_T,
-                                           out_last, grad_feat, grad_records, grad_feats, s)
-                 : launch_bwd<2, float>(records, vals, ranges, feats, C, n, cams, num_views, total_tiles, o, out_T,
-                                        out_last, grad_feat, grad_records, grad_feats, s);
+    } else {
+        e = bf16 ? launch_bwd_channels<uint16_t>(records, vals, ranges, feats, C, n, cams, num_views, total_tiles, o,
+                                                 out_T, out_last, grad_feat, grad_records, grad_feats, s)
+                 : launch_bwd_channels<float>(records, vals, ranges, feats, C, n, cams, num_views, total_tiles, o, out_T,
+                                              out_last, grad_feat, grad_records, grad_feats, s);
+    }
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(preprocess_bwd_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, means, scales,
                        quats, opacity, n, cams, num_views, o, grad_records, grad_means, grad_scales, grad_quats,
