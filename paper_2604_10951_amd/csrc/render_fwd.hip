@@ -2,7 +2,7 @@
 // full (Sec. 3.1 Eq. 2) or with Top-K hard selection (Sec. 3.4).
 //
 // Work decomposition.  A workgroup of four waves renders one 8x8 pixel block
-// and one chunk of at most 64*CPL channels, whatever the binning tile size; the
+// and one chunk of at most 128 channels, whatever the binning tile size; the
 // block's depth-sorted entries are walked in batches of BG.  Tiles of 16x16 and
 // 32x32 pixels hold 4 and 16 blocks, and a block meets only some of its tile's
 // entries (about a third and a tenth on the clustered scenes), so for them the
@@ -20,22 +20,27 @@
 
 namespace {
 
-FS_DEV float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
+// One 16-byte vector of feature elements in LDS, widened to float32.
 template <typename FT>
-FS_DEV float feat_to_f32(FT x);
+struct FeatVec;
 template <>
-FS_DEV float feat_to_f32<float>(float x) { return x; }
+struct FeatVec<float> {
+    static constexpr int kElems = 4;
+    FS_DEV static float at(const uint4& v, int i) {
+        return __uint_as_float(i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w);
+    }
+};
 template <>
-FS_DEV float feat_to_f32<uint16_t>(uint16_t x) { return bf16_to_f32(x); }
+struct FeatVec<uint16_t> {
+    static constexpr int kElems = 8;
+    FS_DEV static float at(const uint4& v, int i) {
+        const uint32_t w = i < 2 ? v.x : i < 4 ? v.y : i < 6 ? v.z : v.w;
+        return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
+    }
+};
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 FS_DEV uint32_t wave_or(uint32_t x) { return __ockl_wfred_or_u32(x); }
-
-// Bytes of a vector load of feature elements (16 B when C allows it).
-template <typename FT, bool VEC>
-struct RowVec {
-    static constexpr int kElems = VEC ? 16 / (int)sizeof(FT) : 1;
-};
 
 // Per-entry data of the extended render (low-pass option, depth and normal
 // outputs), staged once per batch by the entry's own thread.
@@ -70,16 +75,22 @@ FS_DEV void stage_ext(const FsRecord& r, const fs_camera& cam, const uint64_t* _
 //      to LDS by direct global -> LDS loads, issued right after the walk and
 //      consumed one batch later (double buffer), so the load latency is
 //      hidden behind the next batch's alpha pass;
-//   d. accumulate (lanes = channels): each wave adds w * c for its own
-//      pixels, one FMA per channel per (pixel, contributor).
+//   d. accumulate: four lanes per pixel, each owning a quarter of the channels
+//      as 16-byte vectors, so all pixels of a wave advance through their
+//      entries together (pixel after pixel, all lanes on one pixel's channels:
+//      the wave pays every pixel's LDS latency in turn, 0.346 ms for the
+//      1M-surfel 1280x720 C = 128 full blend against 0.27).  The four pixels
+//      of a 16-lane read phase take their vectors in rotated order, so that
+//      their rows, which share banks, are read from different ones.
 // Every pixel sees the same sequence of FP64 transmittance updates and FP32
 // FMAs as in the split Top-K renderer, so the two give identical results.
 constexpr int kQueue = 512;   // entries queued by the filter (a power of two)
-template <int CPL, typename FT, int NW, int BG, bool EXT, bool FILTER>
+template <int NVT, typename FT, int NW, int BG, bool EXT, bool FILTER>
 struct WideShared {
+    static constexpr int kChunk = 4 * NVT * FeatVec<FT>::kElems;   // channels of the workgroup
     FsRecord rec[BG];
     uint32_t recid[2][BG];
-    __align__(16) FT feat[2][BG][64 * CPL];
+    __align__(16) FT feat[2][BG][kChunk];   // rows of two batches; at the end the block's image
     float a[BG][64];              // alpha per accepted (entry, pixel)
     uint32_t amask[2][64];        // per pixel: the batch's accepted entries (double buffer)
     uint8_t rowlist[NW][32];      // per wave: entry of each compacted feature row
@@ -93,8 +104,8 @@ struct WideShared {
     uint32_t item;
 };
 
-template <int CPL, typename FT, int NW, int BG, bool VEC, bool EXT, bool FILTER>
-FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FILTER>& sm,
+template <int NVT, typename FT, int NW, int BG, bool VEC, bool EXT, bool FILTER>
+FS_DEV void render_block_wide(int64_t block, WideShared<NVT, FT, NW, BG, EXT, FILTER>& sm,
                               const FsRecord* __restrict__ records, const uint64_t* __restrict__ keys,
                               const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges,
                               const FT* __restrict__ feats, int C, int64_t n, int64_t num_records,
@@ -107,10 +118,10 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
     static_assert(BG <= 32 && 64 % NW == 0, "batch masks are 32-bit; pixel groups split the 64 pixels evenly");
     constexpr int NT = NW * 64;
     constexpr int PPW = 64 / NW;                             // pixels accumulated per wave
-    constexpr int kChunk = 64 * CPL;
+    constexpr int kVE = FeatVec<FT>::kElems;                 // elements per 16-byte vector
+    constexpr int kChunk = 4 * NVT * kVE;
     constexpr int kQ = FS_RECORD_BYTES / 16;
     constexpr int kRecSlots = (BG * kQ + NT - 1) / NT;
-    constexpr int kVE = RowVec<FT, VEC>::kElems;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
@@ -134,11 +145,16 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
     int cnt = 0;
     int last = -1;
     bool done = !inside;
-    float acc[PPW][CPL];
+    // accumulation: four lanes per pixel, each owning the vectors vec_of
+    const int ap = wave * PPW + (lane >> 2);                 // pixel accumulated by this lane
+    int vec_of[NVT];                                         // the lane's vectors
+    float acc[NVT][kVE];
 #pragma unroll
-    for (int p = 0; p < PPW; ++p)
+    for (int v = 0; v < NVT; ++v) {
+        vec_of[v] = (lane & 3) + 4 * ((v + ((lane >> 2) & 3)) % NVT);
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[p][c] = 0.f;
+        for (int i = 0; i < kVE; ++i) acc[v][i] = 0.f;
+    }
     const double t_stop = o.t_stop;
     const float neg_half_log2e = -0.72134752044448170f;   // -log2(e) / 2
     uint32_t walked = FILTER ? end - start : 0u, fetched = 0;
@@ -213,54 +229,32 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
         fetch_records(nxt_rid);
     };
 
-    // accumulate batch rows already in feat[buf] into the wave's own pixels,
-    // two contributors of a pixel per step (both LDS reads in flight before
-    // the FMAs), in entry order
-    auto accumulate = [&](int buf, uint32_t used, uint32_t mask, uint64_t active_px) {
+    // accumulate batch rows already in feat[buf], each pixel's entries in order
+    // (mask: the pixel's accepted entries); the next entry's weight is read
+    // ahead of the current one's row
+    auto accumulate = [&](int buf, uint32_t used, uint32_t mask) {
+        uint32_t m = mask;
+        int e = m ? __builtin_ctz(m) : 0;
+        float w = sm.w[e][ap];
+        while (m != 0u) {
+            m &= m - 1u;
+            const int en = m ? __builtin_ctz(m) : 0;
+            const float wn = sm.w[en][ap];
+            const uint4* __restrict__ row =
+                reinterpret_cast<const uint4*>(&sm.feat[buf][__popc(used & ((1u << e) - 1u))][0]);
+            uint4 f[NVT];
 #pragma unroll
-        for (int q = 0; q < PPW; ++q) {
-            const int p = wave * PPW + q;
-            if ((active_px >> p) & 1ull) {
-                uint32_t m = __builtin_amdgcn_readlane(mask, p);
-                while (m) {
-                    const int e0 = __builtin_ctz(m);
-                    m &= m - 1u;
-                    const bool two = m != 0u;
-                    const int e1 = two ? __builtin_ctz(m) : e0;
-                    if (two) m &= m - 1u;
-                    const int j0 = __popc(used & ((1u << e0) - 1u));   // row slots
-                    const int j1 = __popc(used & ((1u << e1) - 1u));
-                    const float w0 = sm.w[e0][p];
-                    const float w1 = sm.w[e1][p];
-                    if (CPL == 2 && sizeof(FT) == 4) {
-                        const float2 f0 = *reinterpret_cast<const float2*>(&sm.feat[buf][j0][lane * 2]);
-                        const float2 f1 = *reinterpret_cast<const float2*>(&sm.feat[buf][j1][lane * 2]);
-                        acc[q][0] = fmaf(w0, f0.x, acc[q][0]);
-                        acc[q][CPL - 1] = fmaf(w0, f0.y, acc[q][CPL - 1]);
-                        if (two) {
-                            acc[q][0] = fmaf(w1, f1.x, acc[q][0]);
-                            acc[q][CPL - 1] = fmaf(w1, f1.y, acc[q][CPL - 1]);
-                        }
-                    } else {
-                        float f0[CPL], f1[CPL];
+            for (int v = 0; v < NVT; ++v) f[v] = row[vec_of[v]];
 #pragma unroll
-                        for (int c = 0; c < CPL; ++c) {
-                            f0[c] = feat_to_f32(sm.feat[buf][j0][lane * CPL + c]);
-                            f1[c] = feat_to_f32(sm.feat[buf][j1][lane * CPL + c]);
-                        }
+            for (int v = 0; v < NVT; ++v)
 #pragma unroll
-                        for (int c = 0; c < CPL; ++c) acc[q][c] = fmaf(w0, f0[c], acc[q][c]);
-                        if (two)
-#pragma unroll
-                            for (int c = 0; c < CPL; ++c) acc[q][c] = fmaf(w1, f1[c], acc[q][c]);
-                    }
-                }
-            }
+                for (int i = 0; i < kVE; ++i) acc[v][i] = fmaf(w, FeatVec<FT>::at(f[v], i), acc[v][i]);
+            e = en;
+            w = wn;
         }
     };
 
-    uint32_t p_used = 0u, p_mask = 0u;   // previous batch: entries with rows in flight, lane's accepted entries
-    uint64_t p_active = 0ull;
+    uint32_t p_used = 0u, p_mask = 0u;   // previous batch: entries with rows in flight, accepted ones of pixel ap
     int pbuf = -1;                       // feat buffer of the previous batch (-1: none)
     if constexpr (FILTER) {
         load_val(start);
@@ -375,7 +369,7 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
         // the previous batch's rows (issued before this batch's alpha pass)
         if (VEC) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();   // B: alpha of this batch and rows of the previous batch are in LDS
-        if (pbuf >= 0) accumulate(pbuf, p_used, p_mask, p_active);
+        if (pbuf >= 0) accumulate(pbuf, p_used, p_mask);
         // b. the transmittance walk, identical in every wave: each lane
         //    visits only its pixel's accepted entries, in depth order, with
         //    the next entry's alpha read ahead
@@ -415,7 +409,6 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
             }
         }
         const uint32_t used = wave_or(mask);
-        const uint64_t active_px = __ballot(mask != 0u);
         const bool wactive = !__all(done);
         const int nu = __popc(used);
         // entries walked: to the end of the list once the queue runs dry
@@ -458,8 +451,7 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
             }
         }
         p_used = used;
-        p_mask = mask;
-        p_active = active_px;
+        p_mask = (uint32_t)__shfl((int)mask, ap, 64);
         pbuf = cur;
         qh += (uint32_t)nb;
         if (!wactive) break;   // identical in every wave
@@ -467,7 +459,7 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
     if (pbuf >= 0) {
         if (VEC) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        accumulate(pbuf, p_used, p_mask, p_active);
+        accumulate(pbuf, p_used, p_mask);
     }
 
     if (counters != nullptr && chunk == 0 && wave == 0) {
@@ -496,27 +488,48 @@ FS_DEV void render_block_wide(int64_t block, WideShared<CPL, FT, NW, BG, EXT, FI
             }
         }
     }
-    const int cl = lane * CPL;
+    // the block's image goes out through LDS, as many pixels at a time as the
+    // row buffers hold, so that every (non-temporal: it is not read back by
+    // this kernel) store instruction fills whole lines
+    constexpr int kImage = (int)sizeof(sm.feat) / (kChunk * 4);   // pixels per piece
+    constexpr int kPiece = kImage < 64 ? kImage : 64;
+    static_assert(kPiece % PPW == 0 || PPW % kPiece == 0, "pieces of whole waves or parts of one");
+    float* __restrict__ image = reinterpret_cast<float*>(&sm.feat[0][0][0]);
+    // rows of whole aligned float4 (c0 and clen are multiples of four when C is)
+    const bool vec4 = (C & 3) == 0 && (reinterpret_cast<uintptr_t>(out_feat) & 15u) == 0u;
+    const int per = vec4 ? clen >> 2 : clen;
+    const uint32_t inv = ((1u << 20) + (uint32_t)per - 1u) / (uint32_t)per;   // exact division of t < 64 * 128 by per
+#pragma unroll 1
+    for (int p0 = 0; p0 < 64; p0 += kPiece) {
+        if (pbuf >= 0) {
+            __syncthreads();   // rows, or the previous piece, no longer read
+            if (ap >= p0 && ap < p0 + kPiece) {
 #pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-        const int p = wave * PPW + q;
-        const int qx = bp.x0 + (p & 7), qy = bp.y0 + (p >> 3);
-        if (qx < cam.width && qy < cam.height) {
-            float* dst = out_feat + (cam.pixel_offset + (int64_t)qy * cam.width + qx) * C + c0 + cl;
-            if (CPL == 2 && cl + 1 < clen && ((C & 1) == 0)) {
-                // non-temporal: the image is not read back by this kernel
-                typedef float f32x2 __attribute__((ext_vector_type(2)));
-                __builtin_nontemporal_store(f32x2{acc[q][0], acc[q][CPL - 1]}, reinterpret_cast<f32x2*>(dst));
+                for (int v = 0; v < NVT; ++v)
+#pragma unroll
+                    for (int i = 0; i < kVE; i += 4)
+                        *reinterpret_cast<f32x4*>(image + (ap - p0) * kChunk + vec_of[v] * kVE + i) =
+                            f32x4{acc[v][i], acc[v][i + 1], acc[v][i + 2], acc[v][i + 3]};
+            }
+            __syncthreads();
+        }
+        for (int t = tid; t < kPiece * per; t += NT) {
+            const int p = (int)(((uint64_t)t * inv) >> 20), c = t - p * per;
+            const int qx = bp.x0 + ((p0 + p) & 7), qy = bp.y0 + ((p0 + p) >> 3);
+            if (qx >= cam.width || qy >= cam.height) continue;
+            float* dst = out_feat + (cam.pixel_offset + (int64_t)qy * cam.width + qx) * C + c0;
+            if (vec4) {
+                const f32x4 x = pbuf >= 0 ? *reinterpret_cast<const f32x4*>(image + p * kChunk + 4 * c)
+                                          : f32x4{0.f, 0.f, 0.f, 0.f};
+                __builtin_nontemporal_store(x, reinterpret_cast<f32x4*>(dst + 4 * c));
             } else {
-#pragma unroll
-                for (int c = 0; c < CPL; ++c)
-                    if (cl + c < clen) dst[c] = acc[q][c];
+                __builtin_nontemporal_store(pbuf >= 0 ? image[p * kChunk + c] : 0.f, dst + c);
             }
         }
     }
 }
 
-template <int CPL, typename FT, int NW, int BG, bool VEC, bool EXT, bool FILTER>
+template <int NVT, typename FT, int NW, int BG, bool VEC, bool EXT, bool FILTER>
 __global__ void __launch_bounds__(NW * 64)
 render_wide_kernel(const FsRecord* __restrict__ records, const uint64_t* __restrict__ keys,
                    const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, const FT* __restrict__ feats,
@@ -525,12 +538,12 @@ render_wide_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
                    int32_t* __restrict__ out_last, int32_t* __restrict__ out_idx, float* __restrict__ out_depth,
                    float* __restrict__ out_normal, uint64_t* __restrict__ counters,
                    const uint32_t* __restrict__ order, uint32_t* __restrict__ ticket, uint32_t nblocks) {
-    __shared__ WideShared<CPL, FT, NW, BG, EXT, FILTER> sm;
+    __shared__ WideShared<NVT, FT, NW, BG, EXT, FILTER> sm;
     if (order == nullptr) {
         // the XCDs take one tile row of blocks each in turn: neighbouring
         // blocks share an L2 and dense regions are spread over all XCDs
         const int64_t blk = xcd_remap_chunked(blockIdx.x, gridDim.x, block_row_chunk(cams, S));
-        render_block_wide<CPL, FT, NW, BG, VEC, EXT, FILTER>(blk, sm, records, keys, vals, ranges, feats, C, n, num_records,
+        render_block_wide<NVT, FT, NW, BG, VEC, EXT, FILTER>(blk, sm, records, keys, vals, ranges, feats, C, n, num_records,
                                                      cams, num_views, S, o, out_feat, out_T, out_n, out_last,
                                                      out_idx, out_depth, out_normal, counters);
         return;
@@ -546,7 +559,7 @@ render_wide_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
         __syncthreads();
         const uint32_t it = sm.item * nq + q;
         if (it >= nblocks) break;
-        render_block_wide<CPL, FT, NW, BG, VEC, EXT, FILTER>(order[it], sm, records, keys, vals, ranges, feats, C, n,
+        render_block_wide<NVT, FT, NW, BG, VEC, EXT, FILTER>(order[it], sm, records, keys, vals, ranges, feats, C, n,
                                                      num_records, cams, num_views, S, o, out_feat, out_T, out_n,
                                                      out_last, out_idx, out_depth, out_normal, counters);
     }
@@ -628,7 +641,7 @@ int device_cus() {
     return cus;
 }
 
-template <int CPL, typename FT, int NW, int BG, bool EXT, bool FILTER>
+template <int NVT, typename FT, int NW, int BG, bool EXT, bool FILTER>
 hipError_t launch_wide(const FsRecord* records, const uint64_t* keys, const uint32_t* vals, const uint32_t* ranges,
                        const void* feats, int C, int64_t n, const fs_camera* cams, int num_views, int64_t total_tiles,
                        const fs_opts& o, float* out_feat, float* out_T, int32_t* out_n, int32_t* out_last,
@@ -637,10 +650,11 @@ hipError_t launch_wide(const FsRecord* records, const uint64_t* keys, const uint
     const int sb = o.tile / 8;
     const int64_t blocks = total_tiles * sb * sb;   // 8x8 blocks
     if (blocks >= (int64_t(1) << 32)) return hipErrorInvalidValue;
-    const int chunks = (C + 64 * CPL - 1) / (64 * CPL);
+    constexpr int kChunk = 4 * NVT * FeatVec<FT>::kElems;
+    const int chunks = (C + kChunk - 1) / kChunk;
     const bool vec = (C % (16 / (int)sizeof(FT))) == 0;
-    auto kern = vec ? render_wide_kernel<CPL, FT, NW, BG, true, EXT, FILTER>
-                    : render_wide_kernel<CPL, FT, NW, BG, false, EXT, FILTER>;
+    auto kern = vec ? render_wide_kernel<NVT, FT, NW, BG, true, EXT, FILTER>
+                    : render_wide_kernel<NVT, FT, NW, BG, false, EXT, FILTER>;
     if (o.schedule == FS_SCHED_PERSISTENT && chunks == 1 && blocks <= ws.render_max_blocks) {
         const uint32_t nb = (uint32_t)blocks;
         const hipError_t e = fs_launch_block_order(ranges, sb * sb, nb, ws, s);
@@ -664,7 +678,7 @@ hipError_t launch_wide(const FsRecord* records, const uint64_t* keys, const uint
     return hipGetLastError();
 }
 
-template <int CPL, typename FT>
+template <int NVT, typename FT>
 hipError_t launch_waves(const FsRecord* records, const uint64_t* keys, const uint32_t* vals, const uint32_t* ranges,
                         const void* feats, int C, int64_t n, const fs_camera* cams, int num_views,
                         int64_t total_tiles, const fs_opts& o, float* out_feat, float* out_T, int32_t* out_n,
@@ -676,7 +690,7 @@ hipError_t launch_waves(const FsRecord* records, const uint64_t* keys, const uin
     // their registers
     const bool ext = o.lowpass != 0 || out_depth != nullptr || out_normal != nullptr;
 #define FS_WIDE(B, X, F)                                                                                           \
-    return launch_wide<CPL, FT, 4, B, X, F>(records, keys, vals, ranges, feats, C, n, cams, num_views, total_tiles, \
+    return launch_wide<NVT, FT, 4, B, X, F>(records, keys, vals, ranges, feats, C, n, cams, num_views, total_tiles, \
                                             o, out_feat, out_T, out_n, out_last, out_idx, out_depth, out_normal,    \
                                             counters, ws, s)
     if (o.tile > 8) {   // a block sees a part of its tile's list
@@ -713,14 +727,20 @@ hipError_t fs_launch_render_forward(const FsRecord* records, const uint64_t* key
                                     const FsWorkspace& ws, hipStream_t s) {
     if (total_tiles == 0) return hipSuccess;
     const bool bf16 = o.feat_dtype == FS_FEAT_BF16;
-#define FS_WAVES(CPLv, FTv)                                                                                          \
-    return launch_waves<CPLv, FTv>(records, keys, vals, ranges, feats, C, n, cams, num_views, total_tiles, o,      \
+#define FS_WAVES(NVTv, FTv)                                                                                          \
+    return launch_waves<NVTv, FTv>(records, keys, vals, ranges, feats, C, n, cams, num_views, total_tiles, o,      \
                                    out_feat, out_T, out_n, out_last, out_idx, out_depth, out_normal, counters, ws, s)
-    if (C <= 64) {
-        if (bf16) FS_WAVES(1, uint16_t);
-        FS_WAVES(1, float);
+    // channels per workgroup: 16 to 128 (more run in several, each walking the
+    // lists again), so that narrow images take little LDS
+    if (bf16) {
+        if (C <= 32) FS_WAVES(1, uint16_t);
+        if (C <= 64) FS_WAVES(2, uint16_t);
+        FS_WAVES(4, uint16_t);
     }
-    if (bf16) FS_WAVES(2, uint16_t);
-    FS_WAVES(2, float);
+    if (C <= 16) FS_WAVES(1, float);
+    if (C <= 32) FS_WAVES(2, float);
+    if (C <= 48) FS_WAVES(3, float);
+    if (C <= 64) FS_WAVES(4, float);
+    FS_WAVES(8, float);
 #undef FS_WAVES
 }
