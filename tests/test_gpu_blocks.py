@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (12000, 32, 0, 13, False, "persistent"),
     (12000, 16, 0, 14, False, "grid"),
     (12000, 32, 5, 61, False, "grid"),
+    (12000, 8, 0, 45, False, "persistent"),   # C = 48: rows of 12 lanes
     (12000, 32, 0, 125, True, "persistent"),
     (150, 32, 0, 13, True, "grid"),
     (150, 16, 3, 14, False, "persistent"),
