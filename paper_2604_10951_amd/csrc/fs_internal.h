@@ -1025,12 +1025,13 @@ hipError_t fs_launch_block_order(const uint32_t* ranges, int sb2, uint32_t nbloc
 
 // Selection pass of the split Top-K renderer alone: per-pixel (slot, weight)
 // lists, block row lists and counts in the workspace; out_T, out_last,
-// out_idx and counters optional.
+// out_idx and counters optional.  With out_feat, the blocks that blend nothing
+// get their zero features (C channels).
 hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, const uint32_t* vals,
                                  const uint32_t* ranges, int64_t n, const fs_camera* cams, int num_views,
                                  int64_t total_tiles, const fs_opts& o, float* out_T, int32_t* out_n,
                                  int32_t* out_last, int32_t* out_idx, float* out_depth, float* out_normal,
-                                 uint64_t* counters, const FsWorkspace& ws, hipStream_t s);
+                                 uint64_t* counters, float* out_feat, int C, const FsWorkspace& ws, hipStream_t s);
 
 // Per-Gaussian instance labels (softmax over queries of similarity x
 // proximity); 1 <= Q <= FS_MAX_QUERIES, D % 4 == 0.

@@ -133,6 +133,25 @@ FS_DEV int64_t select_block_of(int64_t nblocks, const fs_camera* cams, int S, in
     return -1;   // fewer long blocks than g + 1
 }
 
+// One wave writes the zero features of an 8x8 block (the part inside the
+// image), row by row: a pixel row's channels are contiguous.  Non-temporal, as
+// the gather's stores.
+FS_DEV void zero_block(float* __restrict__ out_feat, int C, const fs_camera& cam, const BlockPos& bp) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const int lane = (int)threadIdx.x & 63;
+    const int w = cam.width - bp.x0 < 8 ? cam.width - bp.x0 : 8, h = cam.height - bp.y0 < 8 ? cam.height - bp.y0 : 8;
+    const bool vec = C % 4 == 0 && (reinterpret_cast<uintptr_t>(out_feat) & 15u) == 0u;
+    for (int y = 0; y < h; ++y) {
+        float* __restrict__ row = out_feat + (cam.pixel_offset + (int64_t)(bp.y0 + y) * cam.width + bp.x0) * C;
+        if (vec) {
+            for (int t = lane; t < w * C / 4; t += 64)
+                __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(row) + t);
+        } else {
+            for (int t = lane; t < w * C; t += 64) __builtin_nontemporal_store(0.f, row + t);
+        }
+    }
+}
+
 // List layout in the workspace, per 8x8 block b (region b * 64 * K of the
 // pair array): with KC > 0 the pairs of pixel p start at the sum of the
 // counts of pixels 0 .. p - 1 (compact), and nrows[b] = rows | pairs << 16;
@@ -153,7 +172,8 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
                    uint32_t* __restrict__ nrows, float* __restrict__ out_T, int32_t* __restrict__ out_n,
                    int32_t* __restrict__ out_last, int32_t* __restrict__ out_idx, float* __restrict__ out_depth,
                    float* __restrict__ out_normal, uint64_t* __restrict__ counters,
-                   const uint32_t* __restrict__ lng, const uint32_t* __restrict__ lcounts) {
+                   const uint32_t* __restrict__ lng, const uint32_t* __restrict__ lcounts,
+                   float* __restrict__ out_feat, int C) {
     constexpr int BG = kSelBatch;
     constexpr int kQ = FS_RECORD_BYTES / 16;          // float4 per record
     constexpr int kRecSlots = (BG * kQ + 63) / 64;    // record float4 per lane
@@ -521,6 +541,11 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
     } else {
         if (lane == 0) nrows[block] = nslots;
     }
+    // a block that blends nothing gets its zero features here and the gather
+    // skips it: the walks leave the memory idle, and two thirds of the
+    // 1M-surfel 1280x720 C = 128 image are such blocks (select + gather
+    // 60 + 127 us without, 86 + 80 us with; frame 375 -> 355 us)
+    if (out_feat != nullptr && nslots == 0u) zero_block(out_feat, C, cam, bp);
     if (inside) {
         if (out_T) out_T[pix] = (float)T;
         out_n[pix] = cnt;
@@ -652,7 +677,8 @@ constexpr int kNoChannel = 0x7fffffff;
 template <typename FT, int VE, int TPP, bool LABEL>
 __global__ void __launch_bounds__(kGatherThreads)
 topk_gather_general_kernel(const uint2* __restrict__ pairs, const int32_t* __restrict__ counts,
-                           const uint32_t* __restrict__ rows, const FT* __restrict__ feats, int C, int K,
+                           const uint32_t* __restrict__ rows, const uint32_t* __restrict__ nrows,
+                           const FT* __restrict__ feats, int C, int K,
                            const fs_camera* __restrict__ cams, int num_views, int S, int64_t ngroups,
                            float* __restrict__ out_feat, int32_t* __restrict__ out_label,
                            float* __restrict__ out_score) {
@@ -664,6 +690,7 @@ topk_gather_general_kernel(const uint2* __restrict__ pairs, const int32_t* __res
     const int64_t block = g / kGroups;
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
     if (!bp.valid) return;   // uniform over the workgroup
+    if (!LABEL && nrows[block] == 0u) return;   // the selection wrote its zeros
     const fs_camera& cam = cams[bp.view];
     const bool compact = K <= kCompactK;   // the selection's list layout
     if (compact) {
@@ -767,9 +794,9 @@ topk_gather_lds_kernel(const uint2* __restrict__ pairs, const int32_t* __restric
     for (int v = 0; v < NVT; ++v) has_vec[v] = q + v * TPP < nv;
     const uint32_t nr = nrows[block];
     const uint32_t R = nr & 0xffffu, NP = nr >> 16;   // rows and listed pairs of the block
+    if (!LABEL && R == 0u) return;                    // the selection wrote its zeros
     const uint32_t* __restrict__ rowlist = rows + block * 64 * (int64_t)K;
-    // lists, counts and the row list: one round trip (a block
-    // no pixel of which blends anything has R = 0 and only writes zeros)
+    // lists, counts and the row list: one round trip
     if (R > 0)
         for (int t = tid; t < (int)NP; t += kGatherThreads) s_pairs[t] = pairs[block * 64 * (int64_t)K + t];
     if (tid < 64 && R > 0) {
@@ -919,7 +946,8 @@ hipError_t launch_gather(const uint2* pairs, const int32_t* counts, const uint32
     if (groups >= (int64_t(1) << 32)) return hipErrorInvalidValue;
 #define FS_GATHER(TPP)                                                                                            \
     hipLaunchKernelGGL((topk_gather_general_kernel<FT, VE, TPP, LABEL>), dim3((unsigned)groups),                   \
-                       dim3(kGatherThreads), 0, s, pairs, counts, rows, f, C, K, cams, num_views, S, groups, out_feat, \
+                       dim3(kGatherThreads), 0, s, pairs, counts, rows, nrows, f, C, K, cams, num_views, S, groups,  \
+                       out_feat, \
                        out_label, out_score)
     switch (tpp) {
         case 4: FS_GATHER(4); break;
@@ -938,7 +966,7 @@ hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, 
                                  const uint32_t* ranges, int64_t n, const fs_camera* cams, int num_views,
                                  int64_t total_tiles, const fs_opts& o, float* out_T, int32_t* out_n,
                                  int32_t* out_last, int32_t* out_idx, float* out_depth, float* out_normal,
-                                 uint64_t* counters, const FsWorkspace& ws, hipStream_t s) {
+                                 uint64_t* counters, float* out_feat, int C, const FsWorkspace& ws, hipStream_t s) {
     const int sb = o.tile / 8;
     const int64_t nblocks = total_tiles * sb * sb;
     if (ws.topk_pairs == nullptr || ws.topk_rows == nullptr || ws.topk_nrows == nullptr ||
@@ -966,7 +994,7 @@ hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, 
     hipLaunchKernelGGL(FS_SEL_KERN(WPG), dim3((unsigned)(2 * ((nblocks + WPG - 1) / WPG))), dim3(64 * WPG), 0, s,  \
                        records, keys, vals, ranges, (uint32_t)n, n * num_views, cams, num_views, o.tile, o, nblocks,  \
                        ws.topk_pairs, ws.topk_rows, ws.topk_nrows, out_T, out_n, out_last, out_idx, out_depth,        \
-                       out_normal, counters, ws.sel_long, ws.sel_counts)
+                       out_normal, counters, ws.sel_long, ws.sel_counts, out_feat, C)
     // two selection waves per workgroup (one block each): measured on the
     // 1280x720 C = 128 frame, Top-K render 0.1887 / 0.1862 / 0.1951 ms for
     // one, two and four waves per workgroup
@@ -991,7 +1019,8 @@ hipError_t fs_launch_render_topk_split(const FsRecord* records, const uint64_t* 
         (out_feat == nullptr) == (out_label == nullptr))
         return hipErrorInvalidValue;
     hipError_t e = fs_launch_topk_select(records, keys, vals, ranges, n, cams, num_views, total_tiles, o, out_T,
-                                         out_n, out_last, out_idx, out_depth, out_normal, counters, ws, s);
+                                         out_n, out_last, out_idx, out_depth, out_normal, counters, out_feat, C, ws,
+                                         s);
     if (e != hipSuccess) return e;
     const bool bf16 = o.feat_dtype == FS_FEAT_BF16;
     const bool vec = C % (bf16 ? 8 : 4) == 0;
