@@ -534,48 +534,19 @@ preprocess_bwd_kernel(const float* __restrict__ means, const float* __restrict__
 // pixel's (row slot, weight) list and every block's row list; then one
 // workgroup per 8x8 block:
 //   1. D = g . c for every (pixel, contributor): feature rows are staged in
-//      LDS windows (direct global -> LDS loads), TPP threads per pixel each
-//      hold one 16-byte channel vector of g in registers and reduce their
-//      partial dot products with shuffles inside the pixel's group; the same
-//      pass adds w g to per-row LDS accumulators (float atomics), flushed once
-//      per (block, row) to dL/dc;
-//   2. per contribution, all pairs of the block in parallel: alpha from the
-//      record; per pixel (LDS only) the forward's transmittance chain (double
-//      precision, same order) and the suffix sums S = sum_{l > m} w_l D_l;
-//      then the chain to dL/dL and dL/do, summed per row slot in LDS and
-//      flushed once per (block, slot).
+//      registers, TPP threads per row slot, over the slot's pixels; the same
+//      pass sums w g, flushed once per (block, row) to dL/dc;
+//   2. per pixel (LDS only) the forward's transmittance chain (double
+//      precision, same order), the suffix sums S = sum_{l > m} w_l D_l and
+//      dL/dalpha;
+//   3. the chain to dL/dL and dL/do, a thread per pair of the slot, summed over
+//      the slot's threads and flushed once per (block, slot).
 // ---------------------------------------------------------------------------
 constexpr int kGradThreads = 256;
 constexpr int kGradMaxK = 16;
 static_assert(kGradMaxK <= FS_TOPK_COMPACT_K, "the gradient pass reads compact lists");
-constexpr int kGradSlots = 256;   // row slots whose geometry gradients are summed in LDS
 
-template <typename FT>
-struct RowV;
-template <>
-struct RowV<float> {
-    static constexpr int VE = 4;
-    FS_DEV static void get(const uint4& r, float* f) {
-        f[0] = __uint_as_float(r.x);
-        f[1] = __uint_as_float(r.y);
-        f[2] = __uint_as_float(r.z);
-        f[3] = __uint_as_float(r.w);
-    }
-};
-template <>
-struct RowV<uint16_t> {
-    static constexpr int VE = 8;
-    FS_DEV static void get(const uint4& r, float* f) {
-        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            f[2 * i] = __uint_as_float(w[i] << 16);
-            f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
-    }
-};
-
-template <typename FT, int TPP>
+template <typename FT, int TPP, int CPT>
 __global__ void __launch_bounds__(kGradThreads)
 topk_grad_kernel(const FsRecord* __restrict__ records, const uint2* __restrict__ pairs,
                  const int32_t* __restrict__ counts, const uint32_t* __restrict__ rows,
@@ -583,21 +554,18 @@ topk_grad_kernel(const FsRecord* __restrict__ records, const uint2* __restrict__
                  const fs_camera* __restrict__ cams, int num_views, int S, int64_t nblocks, fs_opts o,
                  const float* __restrict__ grad_feat, float* __restrict__ grad_records,
                  float* __restrict__ grad_feats) {
-    constexpr int VE = RowV<FT>::VE;
     constexpr int kGroups = kGradThreads / TPP;   // row slots handled at once
     constexpr int kPairs = 64 * kGradMaxK;
     __shared__ uint2 s_pairs[kPairs];
-    __shared__ float s_D[kPairs];
-    __shared__ float s_S[kPairs];    // alpha, then the transmittance before the contribution
-    __shared__ float s_T2[kPairs];   // alpha
-    __shared__ float s_U[kPairs];    // suffix sums S = sum_{l > m} w_l D_l
+    __shared__ float s_D[kPairs];    // g . c, then dL/dalpha
+    __shared__ float s_al[kPairs];   // alpha
+    __shared__ float s_T[kPairs];    // transmittance before the contribution
     __shared__ int s_soff[kPairs + 1];       // per row slot: first entry of its pair list
     __shared__ int s_sfill[kPairs];          // per row slot: pairs, then the fill cursor
     __shared__ uint16_t s_list[kPairs];      // pair indices p * K + j grouped by row slot
     __shared__ int s_cnt[64];
     __shared__ int s_off[64];                // first pair of each pixel's compact list
     __shared__ int s_wave[kGradThreads / 64];
-    __shared__ float s_grec[kGradSlots][10];   // dL/dL and dL/do of the first kGradSlots row slots
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t block = xcd_remap_chunked(blockIdx.x, nblocks, block_row_chunk(cams, S));
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
@@ -605,9 +573,7 @@ topk_grad_kernel(const FsRecord* __restrict__ records, const uint2* __restrict__
     const uint32_t R = nrows[block] & 0xffffu;   // rows (the high half counts the listed pairs)
     if (R == 0) return;              // no pixel of the block blended anything
     const fs_camera& cam = cams[bp.view];
-    const int nv = C / VE;           // channel vectors per row (C % VE == 0)
     const int q = tid % TPP, grp = tid / TPP;
-    const bool has_vec = q < nv;
     const uint32_t* __restrict__ rowlist = rows + block * 64 * (int64_t)K;
     const int npairs = 64 * K;
     for (int t = tid; t < npairs; t += kGradThreads) s_sfill[t] = 0;
@@ -663,120 +629,122 @@ topk_grad_kernel(const FsRecord* __restrict__ records, const uint2* __restrict__
             s_list[s_soff[slot] + atomicAdd(&s_sfill[slot], 1)] = (uint16_t)t;
         }
     __syncthreads();
-    // 1b. slot-major: a group of TPP threads owns a row slot and one channel
-    //     vector per thread; it reads the feature row once and, over the
-    //     slot's pixels, forms D = g . c (shuffle reduction inside the group)
-    //     and dL/dc = sum w g in registers, flushed once per (block, slot)
+    // 1b. slot-major: a group of TPP threads owns a row slot, thread q the
+    //     channels q, q + TPP, ...; it reads the feature row once and, over the
+    //     slot's pixels, forms D = g . c (lane exchanges inside the group) and
+    //     dL/dc = sum w g in registers, flushed once per (block, slot).  What
+    //     bounds it is the latency of the upstream gradient's rows, so kAhead
+    //     pixels' rows are in flight together, and the flush: the group's
+    //     atomics to a row are contiguous (with four consecutive channels per
+    //     thread each atomic instruction touched every line of the row, and one
+    //     pixel's row was waited for at a time: 399 us for the 200k-surfel,
+    //     640x480, C = 128 gradients against 235, and 166 with pass 3 below).
+    constexpr int kAhead = 4;
     for (uint32_t s0 = 0; s0 < R; s0 += kGroups) {
         const uint32_t slot = s0 + (uint32_t)grp;
-        const bool live = slot < R;   // uniform inside the group
-        float f[VE], acc[VE];
+        if (slot >= R) break;   // uniform inside the group
+        const uint32_t sidx = rowlist[slot];
+        float f[CPT], acc[CPT];
 #pragma unroll
-        for (int i = 0; i < VE; ++i) acc[i] = f[i] = 0.f;
-        uint32_t sidx = 0;
-        if (live) {
-            sidx = rowlist[slot];
-            if (has_vec) RowV<FT>::get(*reinterpret_cast<const uint4*>(feats + (int64_t)sidx * C + q * VE), f);
+        for (int i = 0; i < CPT; ++i) {
+            acc[i] = 0.f;
+            f[i] = q + i * TPP < C ? to_f32(feats[(int64_t)sidx * C + q + i * TPP]) : 0.f;
         }
-        const int a = live ? s_soff[slot] : 0, b = live ? s_soff[slot + 1] : 0;
-        for (int i = a; i < b; ++i) {
-            const int t = s_list[i];
-            const int p = t / K;
-            const int px = bp.x0 + (p & 7), py = bp.y0 + (p >> 3);
-            float gv[VE];
-            if (has_vec) {
-                const float* src = grad_feat + (cam.pixel_offset + (int64_t)py * cam.width + px) * C + q * VE;
+        const int a = s_soff[slot], b = s_soff[slot + 1];
+        // alpha of the slot's pairs (the forward's float value), one per thread
+        {
+            const FsRecord& r = records[(int64_t)bp.view * n + sidx];
+            for (int i = a + q; i < b; i += TPP) {
+                const int t = s_list[i], p = t / K;
+                const FsResp rs = fs_response(r, (double)(bp.x0 + (p & 7) - r.ax), (double)(bp.y0 + (p >> 3) - r.ay));
+                const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
+                s_al[t] = fminf(o.alpha_max, r.o * Gs);
+            }
+        }
+        for (int i0 = a; i0 < b; i0 += kAhead) {
+            int tt[kAhead];
+            float g[kAhead][CPT];
 #pragma unroll
-                for (int e = 0; e < VE; e += 4) {
-                    const float4 v = *reinterpret_cast<const float4*>(src + e);
-                    gv[e] = v.x;
-                    gv[e + 1] = v.y;
-                    gv[e + 2] = v.z;
-                    gv[e + 3] = v.w;
+            for (int u = 0; u < kAhead; ++u) {
+                const bool on = i0 + u < b;
+                tt[u] = s_list[on ? i0 + u : i0];
+                const int p = tt[u] / K;
+                const float* __restrict__ src =
+                    grad_feat + (cam.pixel_offset + (int64_t)(bp.y0 + (p >> 3)) * cam.width + bp.x0 + (p & 7)) * C + q;
+#pragma unroll
+                for (int i = 0; i < CPT; ++i) g[u][i] = on && q + i * TPP < C ? src[i * TPP] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (i0 + u >= b) break;
+                const float w = __uint_as_float(s_pairs[tt[u]].y);
+                float part = 0.f;
+#pragma unroll
+                for (int i = 0; i < CPT; ++i) {
+                    part = fmaf(g[u][i], f[i], part);
+                    acc[i] = fmaf(w, g[u][i], acc[i]);
                 }
-            } else {
 #pragma unroll
-                for (int e = 0; e < VE; ++e) gv[e] = 0.f;
+                for (int d = 1; d < TPP; d <<= 1) part += __uint_as_float(lane_xor32(__float_as_uint(part), d));
+                if (q == 0) s_D[tt[u]] = part;
             }
-            const float w = __uint_as_float(s_pairs[t].y);
-            float part = 0.f;
-#pragma unroll
-            for (int e = 0; e < VE; ++e) {
-                part = fmaf(gv[e], f[e], part);
-                acc[e] = fmaf(w, gv[e], acc[e]);
-            }
-#pragma unroll
-            for (int d = 1; d < TPP; d <<= 1) part += __uint_as_float(lane_xor32(__float_as_uint(part), d));
-            if (q == 0) s_D[t] = part;
         }
-        if (live && has_vec) {
+        float* __restrict__ dst = grad_feats + (int64_t)sidx * C + q;
 #pragma unroll
-            for (int e = 0; e < VE; ++e) atomicAdd(&grad_feats[(int64_t)sidx * C + q * VE + e], acc[e]);
-        }
-    }
-    for (int t = tid; t < kGradSlots * 10; t += kGradThreads) (&s_grec[0][0])[t] = 0.f;
-    // 2. per contribution, all pairs of the block in parallel: (a) alpha (the
-    //    forward's float value); (b) per pixel, from LDS only, the transmittance
-    //    before every contribution (the forward's double-precision product) and
-    //    the suffix sums; (c) the chain to dL/dL and dL/do, summed per row slot.
-    for (int t = tid; t < npairs; t += kGradThreads) {
-        const int p = t / K, j = t - p * K;
-        if (j >= s_cnt[p]) continue;
-        const int px = bp.x0 + (p & 7), py = bp.y0 + (p >> 3);
-        const FsRecord& r = records[(int64_t)bp.view * n + rowlist[s_pairs[t].x]];
-        const FsResp rs = fs_response(r, (double)(px - r.ax), (double)(py - r.ay));
-        const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
-        s_S[t] = fminf(o.alpha_max, r.o * Gs);   // alpha, for now
+        for (int i = 0; i < CPT; ++i)
+            if (q + i * TPP < C) atomicAdd(dst + i * TPP, acc[i]);
     }
     __syncthreads();
+    // 2. per pixel, from LDS only: the transmittance before every contribution
+    //    (the forward's double-precision product), then, back to front, the
+    //    suffix sums and dL/dalpha, left in the place of D
     if (tid < 64) {
-        const int p = tid;
-        const int c = s_cnt[p];
+        const int c = s_cnt[tid], t0 = tid * K;
         double T = 1.0;
         for (int j = 0; j < c; ++j) {
-            const float al = s_S[p * K + j];
-            s_S[p * K + j] = (float)T;   // transmittance before the contribution
-            s_T2[p * K + j] = al;
-            T = T * (1.0 - (double)al);
+            s_T[t0 + j] = (float)T;
+            T = T * (1.0 - (double)s_al[t0 + j]);
         }
         float suffix = 0.f;
         for (int j = c - 1; j >= 0; --j) {
-            const float wD = __uint_as_float(s_pairs[p * K + j].y) * s_D[p * K + j];
-            s_U[p * K + j] = suffix;
-            suffix += wD;
+            const float D = s_D[t0 + j];
+            s_D[t0 + j] = s_T[t0 + j] * D - suffix / (1.f - s_al[t0 + j]);
+            suffix += __uint_as_float(s_pairs[t0 + j].y) * D;
         }
     }
     __syncthreads();
-    for (int t = tid; t < npairs; t += kGradThreads) {
-        const int p = t / K, j = t - p * K;
-        if (j >= s_cnt[p]) continue;
-        const int px = bp.x0 + (p & 7), py = bp.y0 + (p >> 3);
-        const uint32_t slot = s_pairs[t].x;
+    // 3. the chain to dL/dL and dL/do, slot-major again: a thread per pair, sums
+    //    over the group, one flush per (block, slot) (a thread per pair of the
+    //    block with LDS float atomics per slot took 130 of the kernel's 235 us
+    //    with the other passes in their present form)
+    for (uint32_t s0 = 0; s0 < R; s0 += kGroups) {
+        const uint32_t slot = s0 + (uint32_t)grp;
+        if (slot >= R) break;   // uniform inside the group
         const int64_t rid = (int64_t)bp.view * n + rowlist[slot];
         const FsRecord& r = records[rid];
-        const double ddx = (double)(px - r.ax), ddy = (double)(py - r.ay);
-        const FsResp rs = fs_response(r, ddx, ddy);
-        const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
-        const bool clamped = r.o * Gs > o.alpha_max;
-        if (clamped) continue;
-        const float alpha = s_T2[t];
-        const float dalpha = s_S[t] * s_D[t] - s_U[t] / (1.f - alpha);
-        float gg[10];
-        blend_chain(r, rs, ddx, ddy, Gs, dalpha, gg);
-        if (slot < (uint32_t)kGradSlots) {
+        float sum[10];
 #pragma unroll
-            for (int k = 0; k < 10; ++k) atomicAdd(&s_grec[slot][k], gg[k]);
-        } else {
+        for (int k = 0; k < 10; ++k) sum[k] = 0.f;
+        const int b = s_soff[slot + 1];
+        for (int i = s_soff[slot] + q; i < b; i += TPP) {
+            const int t = s_list[i], p = t / K;
+            const double ddx = (double)(bp.x0 + (p & 7) - r.ax), ddy = (double)(bp.y0 + (p >> 3) - r.ay);
+            const FsResp rs = fs_response(r, ddx, ddy);
+            const float Gs = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
+            if (r.o * Gs > o.alpha_max) continue;   // clamped: no gradient
+            float gg[10];
+            blend_chain(r, rs, ddx, ddy, Gs, s_D[t], gg);
 #pragma unroll
-            for (int k = 0; k < 10; ++k) atomicAdd(&grad_records[rid * kGradFloats + k], gg[k]);
+            for (int k = 0; k < 10; ++k) sum[k] += gg[k];
         }
-    }
-    __syncthreads();
-    const int nslot = (int)(R < (uint32_t)kGradSlots ? R : (uint32_t)kGradSlots);
-    for (int t = tid; t < nslot * 10; t += kGradThreads) {
-        const int slot = t / 10, k = t - slot * 10;
-        const float v = s_grec[slot][k];
-        if (v != 0.f) atomicAdd(&grad_records[((int64_t)bp.view * n + rowlist[slot]) * kGradFloats + k], v);
+#pragma unroll
+        for (int d = 1; d < TPP; d <<= 1)
+#pragma unroll
+            for (int k = 0; k < 10; ++k) sum[k] += __uint_as_float(lane_xor32(__float_as_uint(sum[k]), d));
+        float v = 0.f;   // component q of the sums
+#pragma unroll
+        for (int k = 0; k < 10; ++k) v = q == k ? sum[k] : v;
+        if (v != 0.f) atomicAdd(&grad_records[rid * kGradFloats + q], v);
     }
 }
 
@@ -784,22 +752,20 @@ template <typename FT>
 hipError_t launch_topk_grad(const FsRecord* records, const void* feats, int C, int64_t n, const fs_camera* cams,
                             int num_views, int64_t nblocks, const fs_opts& o, const float* grad_feat,
                             float* grad_records, float* grad_feats, const FsWorkspace& ws, hipStream_t s) {
-    constexpr int VE = RowV<FT>::VE;
-    const int nv = C / VE;
-    int tpp = 4;
-    while (tpp < nv) tpp <<= 1;
     const FT* f = static_cast<const FT*>(feats);
-#define FS_GRAD(TPP)                                                                                             \
-    hipLaunchKernelGGL((topk_grad_kernel<FT, TPP>), dim3((unsigned)nblocks), dim3(kGradThreads), 0, s, records,    \
-                       ws.topk_pairs, ws.topk_counts, ws.topk_rows, ws.topk_nrows, f, C, o.topk, n, cams, num_views, \
-                       o.tile, nblocks, o, grad_feat, grad_records, grad_feats)
-    switch (tpp) {
-        case 4: FS_GRAD(4); break;
-        case 8: FS_GRAD(8); break;
-        case 16: FS_GRAD(16); break;
-        case 32: FS_GRAD(32); break;
-        default: FS_GRAD(64); break;
-    }
+#define FS_GRAD(TPP, CPT)                                                                                        \
+    hipLaunchKernelGGL((topk_grad_kernel<FT, TPP, CPT>), dim3((unsigned)nblocks), dim3(kGradThreads), 0, s,        \
+                       records, ws.topk_pairs, ws.topk_counts, ws.topk_rows, ws.topk_nrows, f, C, o.topk, n, cams,  \
+                       num_views, o.tile, nblocks, o, grad_feat, grad_records, grad_feats)
+    // 16 threads per row slot while a thread's channels stay few: the sums then
+    // need no exchange beyond a 16-lane row
+    if (C <= 16) FS_GRAD(16, 1);
+    else if (C <= 32) FS_GRAD(16, 2);
+    else if (C <= 48) FS_GRAD(16, 3);
+    else if (C <= 64) FS_GRAD(16, 4);
+    else if (C <= 128) FS_GRAD(16, 8);
+    else if (C <= 256) FS_GRAD(32, 8);
+    else FS_GRAD(64, 8);
 #undef FS_GRAD
     return hipGetLastError();
 }

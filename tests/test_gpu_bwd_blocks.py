@@ -31,3 +31,22 @@ def test_full_blend_backward_blocks(n, tile, C_extra, dtype):
                              with_abs=True)
     assert np.abs(gpu["feats"]).sum() > 0
     _check(gpu, ref, f"bwd n={n} tile={tile} C={scene.channels} {dtype}")
+
+
+@pytest.mark.parametrize("C,K,dtype", [(16, 8, "f32"), (20, 3, "f32"), (48, 16, "f32"), (64, 8, "f32"), (132, 8, "f32"),
+                                       (256, 4, "f32"), (64, 8, "bf16"), (264, 5, "bf16")])
+def test_topk_backward_channel_groups(C, K, dtype):
+    """Top-K backward at the edges of its channel groups (16 threads per row
+    slot up to 128 channels, 32 up to 256, 64 beyond)."""
+    print(f"[case] topk bwd C={C} K={K} {dtype}", flush=True)
+    scene = scenes.uniform_scene(600, seed=23, feat_channels=C - 3)
+    if dtype == "bf16":
+        import torch
+        scene.feats[:] = torch.from_numpy(scene.feats).bfloat16().float().numpy()
+    cam = scenes.centred_camera(61, 50)
+    g = _upstream(scene, cam, K, seed=4)
+    gpu = _gpu_grads(scene, cam, g, tile=8, topk=K, feat_dtype=dtype)
+    ref = oracle.render_grad(scene.means, scene.scales, scene.quats, scene.opacity, scene.feats, cam, g, K=K,
+                             with_abs=True)
+    assert np.abs(gpu["feats"]).sum() > 0
+    _check(gpu, ref, f"topk bwd C={C} K={K} {dtype}")
