@@ -13,11 +13,10 @@
 //      cursor (any order inside the tile);
 //   2. a sort of every tile's run by (depth key, record), as 64-bit composite
 //      keys: runs of up to kWaveCap entries by one wave each (bitonic network
-//      in the wave's registers), up to kMergeCap by a workgroup (waves sort
-//      512-entry chunks in registers, then pairwise merges in LDS), up to
-//      kLargeCap by a workgroup bitonic network in 64 KB of LDS, longer runs
-//      by a stable one-workgroup LSD radix sort
-//      through global memory.
+//      in the wave's registers), up to kLargeCap by a workgroup (distributed
+//      over equal parts of their depth range in 64 KB of LDS; a bitonic network
+//      there if the depths are bunched), longer runs by a stable one-workgroup
+//      LSD radix sort through global memory.  The scan that writes the ranges also lists the long runs.
 // Every launch is sized from the capacity, not from the device-side pair
 // count, so the sequence can be captured in a graph.
 #include "fs_internal.h"
@@ -25,9 +24,10 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kWaveCap = 512;     // entries per run sorted by one wave (8 per lane, in registers)
+constexpr int kWaveCap = 256;     // entries per run sorted by one wave (4 per lane, in registers): short +
+                                  // long kernels 26.2 us on the 1M-surfel 1280x720 frame, 30.0 with 512,
+                                  // 26.5 with 128; sixteen views 163, 162 and 169
 constexpr int kLargeCap = 8192;   // entries per run sorted in LDS by a workgroup (64 KB)
-constexpr int kMergeCap = 4096;   // entries per run sorted by chunk sorts and merges (two 32 KB buffers)
 constexpr int kLdsTiles = 16384;  // tile counts kept in LDS by the count and scatter kernels
 constexpr int kChunk = 8192;      // pairs per workgroup in the count and scatter kernels
 constexpr int kChunkThreads = 1024;
@@ -39,6 +39,8 @@ constexpr int kScanPart = kThreads * kScanItems;
 constexpr uint64_t kFlagAgg = 1ull << 62;
 constexpr uint64_t kFlagPre = 2ull << 62;
 constexpr uint64_t kValMask = (1ull << 62) - 1;
+constexpr int kLongShift = 31;   // scan values: pairs (fewer than 2^30), long runs above
+constexpr uint64_t kPairMask = (1ull << kLongShift) - 1;
 
 FS_DEV int64_t load_count(const int64_t* num_pairs, int64_t capacity) {
     const int64_t p = *num_pairs;
@@ -137,10 +139,15 @@ FS_DEV uint32_t wave_inclusive_scan(uint32_t x) { return __ockl_wfscan_add_u32(x
 
 // Exclusive scan of the tile counts into ranges (single pass: partitions by
 // atomic ticket, decoupled look-back with one wave reading 64 predecessors
-// per round trip).
+// per round trip).  The same scan numbers the runs longer than kWaveCap (in
+// the upper half of the status words' values) and lists their tiles, their
+// count going to ticket[1] (appended one by one through an atomic counter,
+// which the memory side serialises at about 50 ns each, they held up the
+// short-run kernel: 90 -> 50 us on the sixteen-view frame).
 __global__ void __launch_bounds__(kThreads)
 sort_scan_kernel(const uint32_t* __restrict__ cnt, int64_t tiles, uint32_t* __restrict__ ranges,
-                 uint64_t* __restrict__ status, uint32_t* __restrict__ ticket, int64_t parts) {
+                 uint64_t* __restrict__ status, uint32_t* __restrict__ ticket, int64_t parts,
+                 uint32_t* __restrict__ long_list) {
     __shared__ uint32_t s_part;
     __shared__ uint64_t s_wave[kThreads / 64];
     __shared__ uint64_t s_prefix;
@@ -151,14 +158,15 @@ sort_scan_kernel(const uint32_t* __restrict__ cnt, int64_t tiles, uint32_t* __re
     if (part >= parts) return;
     const int64_t base = part * kScanPart + (int64_t)tid * kScanItems;
     uint32_t c[kScanItems];
-    uint32_t sum = 0;
+    uint32_t sum = 0, longs = 0;
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         c[j] = base + j < tiles ? cnt[base + j] : 0u;
         sum += c[j];
+        longs += c[j] > (uint32_t)kWaveCap ? 1u : 0u;
     }
-    const uint32_t incl = wave_inclusive_scan(sum);
-    if (lane == 63) s_wave[wave] = incl;
+    const uint32_t incl = wave_inclusive_scan(sum), lincl = wave_inclusive_scan(longs);
+    if (lane == 63) s_wave[wave] = incl | (uint64_t)lincl << kLongShift;
     __syncthreads();
     uint64_t wave_excl = 0, total = 0;
     for (int w = 0; w < kThreads / 64; ++w) {
@@ -199,15 +207,19 @@ sort_scan_kernel(const uint32_t* __restrict__ cnt, int64_t tiles, uint32_t* __re
         if (lane == 0) s_prefix = prefix;
     }
     __syncthreads();
-    uint64_t off = s_prefix + wave_excl + (incl - sum);
+    const uint64_t before = s_prefix + wave_excl;
+    uint32_t off = (uint32_t)(before & kPairMask) + (incl - sum);
+    uint32_t slot = (uint32_t)(before >> kLongShift) + (lincl - longs);
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         if (base + j < tiles) {
-            ranges[2 * (base + j)] = (uint32_t)off;
-            ranges[2 * (base + j) + 1] = (uint32_t)(off + c[j]);
+            ranges[2 * (base + j)] = off;
+            ranges[2 * (base + j) + 1] = off + c[j];
+            if (c[j] > (uint32_t)kWaveCap) long_list[slot++] = (uint32_t)(base + j);
         }
         off += c[j];
     }
+    if (part == parts - 1 && tid == 0) ticket[1] = (uint32_t)((s_prefix + total) >> kLongShift);
 }
 
 // Pair i goes to its tile's start plus a cursor, as (depth key, record).
@@ -293,6 +305,34 @@ sort_scatter_kernel(const uint64_t* __restrict__ keys, const uint32_t* __restric
 
 FS_DEV uint64_t composite(uint2 e) { return ((uint64_t)e.x << 32) | e.y; }
 
+// Bitonic sort of one run of 1 <= n <= 64 E entries by one wave, in
+// registers: element i = lane * E + e of the padded run (padding = ~0) is
+// x[e] of its lane.  Compare-exchange partners i ^ j with j < E sit in the
+// same lane; with j >= E they are the same register of lane ^ (j / E),
+// fetched by a shuffle.  The network is the textbook one (stage k, distance
+// j, ascending where i & k == 0), so the result is the sorted run.
+template <int LOGE>
+FS_DEV void sort_run_wave(const uint2* __restrict__ in, uint64_t tile, uint32_t start, int n,
+                          uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    constexpr int E = 1 << LOGE;
+    const int lane = (int)threadIdx.x & 63;
+    uint64_t x[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = lane * E + e;
+        x[e] = i < n ? composite(in[start + i]) : ~0ull;
+    }
+    wave_network<LOGE>(x);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = lane * E + e;
+        if (i < n) {
+            keys[start + i] = (tile << 32) | (x[e] >> 32);
+            vals[start + i] = (uint32_t)x[e];
+        }
+    }
+}
+
 // Bitonic sort of s[0, n2) (n2 a power of two, padding = ~0) by the workgroup.
 template <int NT>
 FS_DEV void bitonic_lds(uint64_t* s, int n2) {
@@ -335,123 +375,141 @@ FS_DEV void sort_run_lds(uint64_t* s, const uint2* __restrict__ in, uint64_t til
     }
 }
 
-// Bitonic sort of one run of 1 <= n <= 64 E entries by one wave, in
-// registers: element i = lane * E + e of the padded run (padding = ~0) is
-// x[e] of its lane.  Compare-exchange partners i ^ j with j < E sit in the
-// same lane; with j >= E they are the same register of lane ^ (j / E),
-// fetched by a shuffle.  The network is the textbook one (stage k, distance
-// j, ascending where i & k == 0), so the result is the sorted run.
-template <int LOGE>
-FS_DEV void sort_run_wave(const uint2* __restrict__ in, uint64_t tile, uint32_t start, int n,
-                          uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    constexpr int E = 1 << LOGE;
-    const int lane = (int)threadIdx.x & 63;
-    uint64_t x[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int i = lane * E + e;
-        x[e] = i < n ? composite(in[start + i]) : ~0ull;
-    }
-    wave_network<LOGE>(x);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int i = lane * E + e;
-        if (i < n) {
-            keys[start + i] = (tile << 32) | (x[e] >> 32);
-            vals[start + i] = (uint32_t)x[e];
-        }
-    }
-}
-
-// Sort of one run of kWaveCap < n <= kMergeCap entries by the workgroup:
-// wave w sorts entries [512 w, 512 w + 512) of the run in registers (padding
-// = ~0, which sorts last), then runs of 512, 1024, ... are merged pairwise
-// through LDS, ping-ponging between the two halves of s.  Every thread
-// makes 8 outputs per round: it finds, by binary search along the merge
-// path, how many of its first output's predecessors come from the left run
-// (keys are distinct), then merges 8 entries.  At most three rounds.
-FS_DEV void sort_run_merge(uint64_t* s, const uint2* __restrict__ in, uint64_t tile, uint32_t start, int n,
-                           uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    static_assert(kLongThreads * 8 >= kMergeCap && 2 * kMergeCap <= kLargeCap, "buffers of the merge rounds");
+// Sort of one run of n <= kLargeCap entries by the workgroup in one
+// distribution step: the depth keys' range is cut into kBuckets equal parts (a
+// monotone map), entries go to LDS grouped by part, and an entry's place inside
+// its part is the number of the part's entries before it, counted directly.  A
+// run's depths spread over the parts (a few entries each), so an entry costs an
+// LDS atomic or two and a few reads, where the sorted chunks and merges of
+// before cost it 20 to 45 exchanges and 20 dependent reads: long runs of the
+// sixteen-view frame 217 -> 112 us, of the 1M-surfel 1280x720 frame 26 -> 11.5 (runs over 512).
+// Returns false, having written nothing, if a part holds more than kPartMax
+// entries (depths bunched beyond the map's resolution): uniform over the
+// workgroup.  Up to two entries per thread stay in registers (HELD); longer
+// runs are read again from memory in every phase.
+constexpr int kBuckets = kLongThreads;
+constexpr uint32_t kPartMax = 64;
+struct BucketShared {
+    uint32_t part[kBuckets + 1];   // entries, then first place, of every part
+    uint32_t fill[kBuckets];       // entries placed so far
+    uint32_t red[2 * (kLongThreads / 64)];
+};
+template <bool HELD>
+FS_DEV bool sort_run_buckets(uint64_t* s, BucketShared& b, const uint2* __restrict__ in, uint64_t tile, uint32_t start,
+                             int n, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    constexpr int kWaves = kLongThreads / 64;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = (n + kWaveCap - 1) / kWaveCap;   // sorted chunks, 2 .. kMergeCap / kWaveCap
-    const int N = m * kWaveCap;
-    uint64_t* a = s;
-    uint64_t* b = s + kMergeCap;
-    if (wave < m) {
-        uint64_t x[8];
-        const int base = wave * kWaveCap + lane * 8;
+    const int i1 = tid + kLongThreads;
+    uint2 x0 = make_uint2(0u, 0u), x1 = make_uint2(0u, 0u);
+    uint32_t lo = ~0u, hi = 0u;
+    // f(entry) for every entry of this thread
+    auto each = [&](auto&& f) {
+        if constexpr (HELD) {
+            if (tid < n) f(x0);
+            if (i1 < n) f(x1);
+        } else {
+            for (int i = tid; i < n; i += kLongThreads) f(in[start + i]);
+        }
+    };
+    if constexpr (HELD) {
+        if (tid < n) x0 = in[start + tid];
+        if (i1 < n) x1 = in[start + i1];
+    }
+    each([&](const uint2& x) {
+        lo = x.x < lo ? x.x : lo;
+        hi = x.x > hi ? x.x : hi;
+    });
+    lo = __ockl_wfred_min_u32(lo);
+    hi = __ockl_wfred_max_u32(hi);
+    if (lane == 0) {
+        b.red[wave] = lo;
+        b.red[kWaves + wave] = hi;
+    }
+    b.part[tid] = 0u;
+    b.fill[tid] = 0u;
+    __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = base + e < n ? composite(in[start + base + e]) : ~0ull;
-        wave_network<3>(x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a[base + e] = x[e];
+    for (int w = 0; w < kWaves; ++w) {
+        lo = b.red[w] < lo ? b.red[w] : lo;
+        hi = b.red[kWaves + w] > hi ? b.red[kWaves + w] : hi;
+    }
+    const float scale = hi > lo ? (float)(kBuckets - 1) / (float)(hi - lo) : 0.f;
+    auto part_of = [&](uint32_t d) {
+        const int q = (int)((float)(d - lo) * scale);
+        return q < kBuckets ? q : kBuckets - 1;
+    };
+    each([&](const uint2& x) { atomicAdd(&b.part[part_of(x.x)], 1u); });
+    __syncthreads();
+    const uint32_t c = b.part[tid];
+    const uint32_t incl = wave_inclusive_scan(c), cmax = __ockl_wfred_max_u32(c);
+    if (lane == 63) {   // (the last readers of red ended before the barrier)
+        b.red[wave] = incl;
+        b.red[kWaves + wave] = cmax;
     }
     __syncthreads();
-    for (int width = kWaveCap; width < N; width *= 2) {
-        const int o = tid * 8;   // first output of this thread
-        if (o < N) {
-            const int ps = (o / (2 * width)) * (2 * width);
-            const int na = N - ps < width ? N - ps : width;
-            const int nb = N - ps - na < width ? N - ps - na : width;
-            const uint64_t* A = a + ps;
-            const uint64_t* B = A + na;
-            const int d = o - ps;
-            int lo = d - nb > 0 ? d - nb : 0, hi = d < na ? d : na;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (A[mid] < B[d - 1 - mid])
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            int i = lo, j = d - lo;
+    uint32_t first = incl - c, most = 0u;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const bool take_a = j >= nb || (i < na && A[i] < B[j]);
-                b[o + e] = take_a ? A[i] : B[j];
-                i += take_a ? 1 : 0;
-                j += take_a ? 0 : 1;
-            }
-        }
+    for (int w = 0; w < kWaves; ++w) {
+        first += w < wave ? b.red[w] : 0u;
+        most = b.red[kWaves + w] > most ? b.red[kWaves + w] : most;
+    }
+    if (most > kPartMax) return false;
+    b.part[tid] = first;
+    if (tid == kBuckets - 1) b.part[kBuckets] = first + c;
+    __syncthreads();
+    each([&](const uint2& x) {
+        const int q = part_of(x.x);
+        s[b.part[q] + atomicAdd(&b.fill[q], 1u)] = composite(x);
+    });
+    __syncthreads();
+    auto place_of = [&](const uint2& x) {
+        const int q = part_of(x.x);
+        const uint32_t p0 = b.part[q], p1 = b.part[q + 1];
+        const uint64_t v = composite(x);
+        uint32_t r = p0;
+        for (uint32_t p = p0; p < p1; ++p) r += s[p] < v ? 1u : 0u;
+        return r;
+    };
+    if constexpr (HELD) {
+        const uint32_t r0 = tid < n ? place_of(x0) : 0u, r1 = i1 < n ? place_of(x1) : 0u;
         __syncthreads();
-        uint64_t* t = a;
-        a = b;
-        b = t;
+        if (tid < n) s[r0] = composite(x0);
+        if (i1 < n) s[r1] = composite(x1);
+        __syncthreads();
+        for (int i = tid; i < n; i += kLongThreads) {
+            const uint64_t v = s[i];
+            keys[start + i] = (tile << 32) | (v >> 32);
+            vals[start + i] = (uint32_t)v;
+        }
+    } else {
+        each([&](const uint2& x) {
+            const uint32_t r = place_of(x);
+            keys[start + r] = (tile << 32) | x.x;
+            vals[start + r] = x.y;
+        });
     }
-    for (int i = tid; i < n; i += kLongThreads) {
-        const uint64_t c = a[i];
-        keys[start + i] = (tile << 32) | (c >> 32);
-        vals[start + i] = (uint32_t)c;
-    }
+    return true;
 }
 
 // One wave per tile: runs of up to kWaveCap entries are sorted in the wave's
-// registers (1, 2, 4 or 8 entries per lane by run length); longer runs are
-// appended to the list the long-run kernel works through.
+// registers (1, 2 or 4 entries per lane by run length); longer ones are on
+// the list the long-run kernel works through.
 __global__ void __launch_bounds__(kThreads)
 sort_short_runs_kernel(const uint2* __restrict__ in, const uint32_t* __restrict__ ranges, int64_t tiles,
-                       uint64_t* __restrict__ keys, uint32_t* __restrict__ vals, uint32_t* __restrict__ long_list,
-                       uint32_t* __restrict__ long_count) {
-    static_assert(kWaveCap == 512, "runs up to 8 entries per lane");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                       uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    static_assert(kWaveCap == 256, "runs up to 4 entries per lane");
+    const int wave = threadIdx.x >> 6;
     const int64_t t = (int64_t)blockIdx.x * (kThreads / 64) + wave;
     if (t >= tiles) return;   // uniform per wave
     const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
     const int n = (int)(end - start);
-    if (n == 0) return;
-    if (n > kWaveCap) {
-        if (lane == 0) long_list[atomicAdd(long_count, 1u)] = (uint32_t)t;
-        return;
-    }
+    if (n == 0 || n > kWaveCap) return;
     if (n <= 64)
         sort_run_wave<0>(in, (uint64_t)t, start, n, keys, vals);
     else if (n <= 128)
         sort_run_wave<1>(in, (uint64_t)t, start, n, keys, vals);
-    else if (n <= 256)
-        sort_run_wave<2>(in, (uint64_t)t, start, n, keys, vals);
     else
-        sort_run_wave<3>(in, (uint64_t)t, start, n, keys, vals);
+        sort_run_wave<2>(in, (uint64_t)t, start, n, keys, vals);
 }
 
 // Stable LSD radix sort of one run through global memory, 8-bit digits of the
@@ -529,8 +587,8 @@ FS_DEV void sort_run_global(uint2* a, uint2* b, uint64_t tile, uint32_t start, u
     }
 }
 
-// Runs longer than kWaveCap, from the list: up to kLargeCap entries by a
-// workgroup bitonic network in LDS, longer ones by the global radix sort.
+// Runs longer than kWaveCap, from the list: up to kLargeCap entries in LDS,
+// longer ones by the global radix sort.
 // Two workgroups per CU (64 VGPRs at most) keep every long run of a frame
 // in flight at once.
 __global__ void __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(8)))
@@ -538,15 +596,16 @@ sort_long_runs_kernel(uint2* __restrict__ in, const uint32_t* __restrict__ range
                       const uint32_t* __restrict__ long_list, const uint32_t* __restrict__ long_count,
                       uint64_t* keys, uint32_t* __restrict__ vals) {
     __shared__ uint64_t s[kLargeCap];
+    __shared__ BucketShared parts;
     const uint32_t count = *long_count;
     for (uint32_t it = blockIdx.x; it < count; it += gridDim.x) {
         const uint64_t t = long_list[it];
         const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
         const uint32_t n = end - start;
-        if (n <= (uint32_t)kMergeCap) {
-            sort_run_merge(s, in, t, start, (int)n, keys, vals);
-        } else if (n <= (uint32_t)kLargeCap) {
-            sort_run_lds<kLongThreads>(s, in, t, start, (int)n, keys, vals);
+        if (n <= (uint32_t)kLargeCap) {
+            const bool done = n <= 2u * kLongThreads ? sort_run_buckets<true>(s, parts, in, t, start, (int)n, keys, vals)
+                                                     : sort_run_buckets<false>(s, parts, in, t, start, (int)n, keys, vals);
+            if (!done) sort_run_lds<kLongThreads>(s, in, t, start, (int)n, keys, vals);
         } else {
             // the run's own slice of the key array is the radix passes' second
             // buffer; LDS holds their counters
@@ -581,12 +640,12 @@ hipError_t fs_launch_sort(uint64_t* keys, uint32_t* vals, int64_t capacity, cons
     hipLaunchKernelGGL(sort_count_kernel, dim3(pblocks), dim3(kChunkThreads), 0, s, keys, num_pairs, capacity,
                        total_tiles, ws.tile_cnt);
     hipLaunchKernelGGL(sort_scan_kernel, dim3((unsigned)parts), dim3(kThreads), 0, s, ws.tile_cnt, total_tiles, ranges,
-                       ws.sort_status, ws.sort_ticket, parts);
+                       ws.sort_status, ws.sort_ticket, parts, ws.long_list);
     hipLaunchKernelGGL(sort_scatter_kernel, dim3(pblocks), dim3(kChunkThreads), 0, s, keys, vals, num_pairs, capacity,
                        total_tiles, ranges, ws.tile_fill, ws.runs);
     const unsigned sblocks = (unsigned)((total_tiles + kThreads / 64 - 1) / (kThreads / 64));
     hipLaunchKernelGGL(sort_short_runs_kernel, dim3(sblocks), dim3(kThreads), 0, s, ws.runs, ranges, total_tiles, keys,
-                       vals, ws.long_list, ws.sort_ticket + 1);
+                       vals);
     hipLaunchKernelGGL(sort_long_runs_kernel, dim3(kLongGrid), dim3(kLongThreads), 0, s, ws.runs, ranges, ws.long_list,
                        ws.sort_ticket + 1, keys, vals);
     return hipGetLastError();
