@@ -270,9 +270,9 @@ bin_kernel(const float* __restrict__ means, const float* __restrict__ scales, co
             continue;
         }
         if (c[j] == 0 || o0 >= (uint64_t)capacity) continue;
-        const int v = (int)(r / n);
+        const uint32_t v = (uint32_t)r / (uint32_t)n;   // fewer than 2^32 records
         const fs_camera& cam = cams[v];
-        const uint32_t tiles_x = ((uint32_t)cam.width + (uint32_t)S - 1u) / (uint32_t)S;
+        const uint32_t tiles_x = ((uint32_t)cam.width + (uint32_t)S - 1u) >> __builtin_ctz(S);
         const uint4 cache = cch[j];
         const uint64_t zk = cache.x;
         auto emit = [&](int k, uint32_t tx, uint32_t ty) {
@@ -314,10 +314,10 @@ bin_overflow_kernel(const float* __restrict__ means, const float* __restrict__ s
     for (uint32_t k = blockIdx.x * kThreads + threadIdx.x; k < total; k += gridDim.x * kThreads) {
         const uint2 e = overflow[k];
         const int64_t r = e.x;
-        const int v = (int)(r / n);
+        const uint32_t v = (uint32_t)r / (uint32_t)n;   // fewer than 2^32 records
         const int64_t i = r - (int64_t)v * n;
         const fs_camera& cam = cams[v];
-        const int tiles_x = (cam.width + S - 1) / S;
+        const int tiles_x = (cam.width + S - 1) >> __builtin_ctz(S);
         FsGeo g;
         FsFootprint fp;
         if (!fs_project(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], cam, (double)o.alpha_min, g))

@@ -213,20 +213,22 @@ FS_DEV void fs_conic(const double H[9], double k2, int ax, int ay, FsConic& q) {
 }
 
 // Continuous extent of the ellipse (anchor-relative): dx in [x0, x1], dy in
-// [y0, y1].  Returns false if the conic is not a bounded ellipse.
+// [y0, y1].  Returns false if the conic is not a bounded ellipse.  Only
+// candidate ranges widened by far more than its rounding come from it (a pixel,
+// or 1e-3 px for the tiles a line can reach), so one reciprocal of the
+// determinant and the roots of fs_sqrt_line do (relative errors of 1e-15 and
+// 1e-13).
 FS_DEV bool fs_conic_extent(const FsConic& q, double e[4]) {
     const double det = q.A * q.C - q.B * q.B;
     if (!(q.A > 0.0) || !(q.C > 0.0) || !(det > 0.0)) return false;
     const double bx = q.B * q.E - q.C * q.D, by = q.B * q.D - q.A * q.E;
-    double rx = bx * bx + det * (q.E * q.E - q.C * q.F);
-    double ry = by * by + det * (q.D * q.D - q.A * q.F);
-    rx = rx > 0.0 ? rx : 0.0;
-    ry = ry > 0.0 ? ry : 0.0;
-    const double sx = sqrt(rx), sy = sqrt(ry);
-    e[0] = (bx - sx) / det;
-    e[1] = (bx + sx) / det;
-    e[2] = (by - sy) / det;
-    e[3] = (by + sy) / det;
+    const double sx = fs_sqrt_line(bx * bx + det * (q.E * q.E - q.C * q.F));
+    const double sy = fs_sqrt_line(by * by + det * (q.D * q.D - q.A * q.F));
+    const double rd = fs_rcp_approx(det);
+    e[0] = (bx - sx) * rd;
+    e[1] = (bx + sx) * rd;
+    e[2] = (by - sy) * rd;
+    e[3] = (by + sy) * rd;
     return fs_finite(e[0]) && fs_finite(e[1]) && fs_finite(e[2]) && fs_finite(e[3]);
 }
 
@@ -237,8 +239,11 @@ struct FsFootprint {
     double k2;
     FsConic q;
     int px0, px1, py0, py1;   // candidate pixel range (inclusive), clamped to the image
+    double ext[4];            // the conic's continuous extent, clamped to +-4e6 px
+    bool bounded;             // it is one (else the range is the whole image)
 };
 
+FS_DEV int fs_clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 FS_DEV int fs_clampi(long long v, int lo, int hi) { return (int)(v < lo ? lo : (v > hi ? hi : v)); }
 
 // Build the footprint: anchor at the pixel containing the projected centre
@@ -251,11 +256,12 @@ FS_DEV bool fs_footprint(const FsGeo& g, int W, int Hh, FsFootprint& fp) {
     const double lim = 1.0e6;
     const double cmx = mx < -lim ? -lim : (mx > lim ? lim : mx);
     const double cmy = my < -lim ? -lim : (my > lim ? lim : my);
-    const int ax = fs_clampi((long long)floor(cmx), 0, W - 1);
-    const int ay = fs_clampi((long long)floor(cmy), 0, Hh - 1);
+    const int ax = fs_clampi((int)floor(cmx), 0, W - 1);
+    const int ay = fs_clampi((int)floor(cmy), 0, Hh - 1);
     fs_conic(fp.H, fp.k2, ax, ay, fp.q);
-    double e[4];
-    if (!fs_conic_extent(fp.q, e)) {
+    double* e = fp.ext;
+    fp.bounded = fs_conic_extent(fp.q, e);
+    if (!fp.bounded) {
         fp.px0 = 0;
         fp.px1 = W - 1;
         fp.py0 = 0;
@@ -265,12 +271,13 @@ FS_DEV bool fs_footprint(const FsGeo& g, int W, int Hh, FsFootprint& fp) {
     const double big = 4.0e6;
     for (int j = 0; j < 4; ++j) e[j] = e[j] < -big ? -big : (e[j] > big ? big : e[j]);
     // pixel centre px + .5 = ax + .5 + dx  ->  px = ax + dx
-    fp.px0 = fs_clampi((long long)ceil(e[0]) + ax - 1, 0, W - 1);
-    fp.px1 = fs_clampi((long long)floor(e[1]) + ax + 1, 0, W - 1);
-    fp.py0 = fs_clampi((long long)ceil(e[2]) + ay - 1, 0, Hh - 1);
-    fp.py1 = fs_clampi((long long)floor(e[3]) + ay + 1, 0, Hh - 1);
-    if ((long long)floor(e[1]) + ax + 1 < 0 || (long long)ceil(e[0]) + ax - 1 > W - 1) return false;
-    if ((long long)floor(e[3]) + ay + 1 < 0 || (long long)ceil(e[2]) + ay - 1 > Hh - 1) return false;
+    const int x0 = (int)ceil(e[0]) + ax - 1, x1 = (int)floor(e[1]) + ax + 1;
+    const int y0 = (int)ceil(e[2]) + ay - 1, y1 = (int)floor(e[3]) + ay + 1;
+    fp.px0 = fs_clampi(x0, 0, W - 1);
+    fp.px1 = fs_clampi(x1, 0, W - 1);
+    fp.py0 = fs_clampi(y0, 0, Hh - 1);
+    fp.py1 = fs_clampi(y1, 0, Hh - 1);
+    if (x1 < 0 || x0 > W - 1 || y1 < 0 || y0 > Hh - 1) return false;
     return fp.px0 <= fp.px1 && fp.py0 <= fp.py1;
 }
 
@@ -342,27 +349,28 @@ FS_DEV bool fs_conic_line(const FsConic& q, Pin&& pin, bool rows, int l, int lo_
         s1 = s2;
         s2 = tmp;
     }
-    if (!(s1 > -4.0e6)) s1 = -4.0e6;
-    if (!(s2 < 4.0e6)) s2 = 4.0e6;
+    // (fmin and fmax take the bound for a NaN)
+    s1 = fmin(fmax(s1, -4.0e6), 4.0e6);
+    s2 = fmax(fmin(s2, 4.0e6), -4.0e6);
     // centres strictly inside: s in [ceil(s1), floor(s2)]
     const double cs1 = ceil(s1), fs2 = floor(s2);
-    long long L = (long long)cs1 + anchor_s, Hi = (long long)fs2 + anchor_s;
+    int L = (int)cs1 + anchor_s, Hi = (int)fs2 + anchor_s;
     // re-decide endpoints within eps of the conic
     if (cs1 - s1 < eps) {                     // first centre barely inside
-        if (L >= lo_lim && L <= hi_lim && !pin((int)L)) ++L;
+        if (L >= lo_lim && L <= hi_lim && !pin(L)) ++L;
     } else if (1.0 - (cs1 - s1) < eps) {      // centre before it barely outside
-        if (L - 1 >= lo_lim && L - 1 <= hi_lim && pin((int)(L - 1))) --L;
+        if (L - 1 >= lo_lim && L - 1 <= hi_lim && pin(L - 1)) --L;
     }
     if (s2 - fs2 < eps) {
-        if (Hi >= lo_lim && Hi <= hi_lim && !pin((int)Hi)) --Hi;
+        if (Hi >= lo_lim && Hi <= hi_lim && !pin(Hi)) --Hi;
     } else if (1.0 - (s2 - fs2) < eps) {
-        if (Hi + 1 >= lo_lim && Hi + 1 <= hi_lim && pin((int)(Hi + 1))) ++Hi;
+        if (Hi + 1 >= lo_lim && Hi + 1 <= hi_lim && pin(Hi + 1)) ++Hi;
     }
     if (L < lo_lim) L = lo_lim;
     if (Hi > hi_lim) Hi = hi_lim;
     if (L > Hi) return false;
-    lo = (int)L;
-    hi = (int)Hi;
+    lo = L;
+    hi = Hi;
     return true;
 }
 
@@ -388,37 +396,38 @@ FS_DEV void fs_sweep_tiles(const FsFootprint& fp, int S, Visit&& visit) {
     const bool rows = (fp.py1 - fp.py0) <= (fp.px1 - fp.px0);
     const int l0 = rows ? fp.py0 : fp.px0, l1 = rows ? fp.py1 : fp.px1;      // lines
     const int s0 = rows ? fp.px0 : fp.py0, s1 = rows ? fp.px1 : fp.py1;      // along-line range
-    const int ts0 = s0 / S, ts1 = s1 / S;
+    // tile sides are powers of two; divisions by a variable side took a quarter
+    // of preprocess's vector instructions
+    const int ls = __builtin_ctz(S);
+    const int ts0 = s0 >> ls, ts1 = s1 >> ls;
+    // the conic with the lines' axis as its second one, whichever that is
+    FsConic q;
+    q.A = rows ? fp.q.A : fp.q.C;
+    q.B = fp.q.B;
+    q.C = rows ? fp.q.C : fp.q.A;
+    q.D = rows ? fp.q.D : fp.q.E;
+    q.E = rows ? fp.q.E : fp.q.D;
+    q.F = fp.q.F;
+    q.ax = rows ? fp.q.ax : fp.q.ay;
+    q.ay = rows ? fp.q.ay : fp.q.ax;
     // the line through the conic's centre (the middle of the range if the
-    // conic is not a bounded ellipse)
+    // conic is not a bounded ellipse), and the tiles any line can reach: the
+    // conic's extent along the lines, with a margin of 1e-3 px (far beyond its
+    // rounding), within [s0, s1]; for a nearly degenerate conic (det < 1e-6 A C,
+    // an extent sensitive to the coefficients' rounding) the whole candidate
+    // range
     int lc = (l0 + l1) >> 1;
-    {
-        const FsConic& q = fp.q;
-        const double det = q.A * q.C - q.B * q.B;
-        if (q.A > 0.0 && q.C > 0.0 && det > 0.0) {
-            const double cen = rows ? (q.B * q.D - q.A * q.E) / det + (double)q.ay
-                                    : (q.B * q.E - q.C * q.D) / det + (double)q.ax;
-            if (cen > (double)l0 && cen < (double)l1) lc = (int)rint(cen);
-        }
-    }
-    // the tiles any line can reach: the conic's extent along the lines, with
-    // a margin of 1e-3 px (far beyond its rounding), within [s0, s1]; for a
-    // nearly degenerate conic (det < 1e-6 A C, an extent sensitive to the
-    // coefficients' rounding) the whole candidate range
     int tt0 = ts0, tt1 = ts1;
-    {
-        const FsConic& q = fp.q;
-        double e[4];
-        if (q.A * q.C - q.B * q.B > 1e-6 * (q.A * q.C) && fs_conic_extent(q, e)) {
-            const double a0 = rows ? e[0] : e[2], a1 = rows ? e[1] : e[3];
-            const int anchor = rows ? fp.q.ax : fp.q.ay;
-            if (a0 > -4.0e6 && a1 < 4.0e6) {
-                const long long lo = (long long)ceil(a0 - 1e-3) + anchor, hi = (long long)floor(a1 + 1e-3) + anchor;
-                const int clo = fs_clampi(lo, s0, s1), chi = fs_clampi(hi, s0, s1);
-                if (clo <= chi) {
-                    tt0 = clo / S;
-                    tt1 = chi / S;
-                }
+    if (fp.bounded) {
+        const double cen = 0.5 * (rows ? fp.ext[2] + fp.ext[3] : fp.ext[0] + fp.ext[1]) + (double)q.ay;
+        if (cen > (double)l0 && cen < (double)l1) lc = (int)rint(cen);
+        const double a0 = rows ? fp.ext[0] : fp.ext[2], a1 = rows ? fp.ext[1] : fp.ext[3];
+        if (q.A * q.C - q.B * q.B > 1e-6 * (q.A * q.C) && a0 > -4.0e6 && a1 < 4.0e6) {
+            const int clo = fs_clampi((int)ceil(a0 - 1e-3) + q.ax, s0, s1);
+            const int chi = fs_clampi((int)floor(a1 + 1e-3) + q.ax, s0, s1);
+            if (clo <= chi) {
+                tt0 = clo >> ls;
+                tt1 = chi >> ls;
             }
         }
     }
@@ -428,17 +437,18 @@ FS_DEV void fs_sweep_tiles(const FsFootprint& fp, int S, Visit&& visit) {
         const int f1 = tt1 - wbase < 63 ? tt1 - wbase : 63;
         const uint64_t full = f0 > f1 ? 0ull
                                       : ((f1 == 63 ? ~0ull : ((1ull << (f1 + 1)) - 1ull)) & ~((1ull << f0) - 1ull));
-        for (int tl = l0 / S; tl <= l1 / S; ++tl) {
+        for (int tl = l0 >> ls; tl <= l1 >> ls; ++tl) {
             uint64_t mask = 0;
-            const int la = tl * S > l0 ? tl * S : l0;
-            const int lb = tl * S + S - 1 < l1 ? tl * S + S - 1 : l1;
+            const int la = (tl << ls) > l0 ? tl << ls : l0;
+            const int lb = (tl << ls) + S - 1 < l1 ? (tl << ls) + S - 1 : l1;
             const int lm = lc < la ? la : (lc > lb ? lb : lc);
             for (int k = 0; k <= lb - la && mask != full; ++k) {
                 // lm, lm + 1, .., lb, then lm - 1, .., la
                 const int l = lm + k <= lb ? lm + k : lm - (k - (lb - lm));
                 int lo, hi;
-                if (!fs_line_interval(fp, rows, l, s0, s1, lo, hi)) continue;
-                int t1 = lo / S - wbase, t2 = hi / S - wbase;
+                auto pin = [&](int t) -> bool { return fs_pixel_in(fp.H, fp.k2, rows ? t : l, rows ? l : t); };
+                if (!fs_conic_line(q, pin, true, l, s0, s1, lo, hi)) continue;
+                int t1 = (lo >> ls) - wbase, t2 = (hi >> ls) - wbase;
                 if (t2 < 0 || t1 > 63) continue;
                 t1 = t1 < 0 ? 0 : t1;
                 t2 = t2 > 63 ? 63 : t2;
@@ -642,15 +652,16 @@ FS_DEV void fs_sweep_tiles_ext(const FsFootprint& fp, const FsAssign& a, int S, 
     const bool rows = (ar[3] - ar[2]) <= (ar[1] - ar[0]);
     const int l0 = rows ? ar[2] : ar[0], l1 = rows ? ar[3] : ar[1];
     const int s0 = rows ? ar[0] : ar[2], s1 = rows ? ar[1] : ar[3];
-    const int ts0 = s0 / S, ts1 = s1 / S;
+    const int ls = __builtin_ctz(S);
+    const int ts0 = s0 >> ls, ts1 = s1 >> ls;
     const bool use_exact = !a.lin && a.exact_ok, use_lin = a.lin && a.lin_ok, use_disc = a.disc;
     for (int wbase = ts0; wbase <= ts1; wbase += 64) {
-        for (int tl = l0 / S; tl <= l1 / S; ++tl) {
+        for (int tl = l0 >> ls; tl <= l1 >> ls; ++tl) {
             uint64_t mask = 0;
-            const int la = tl * S > l0 ? tl * S : l0;
-            const int lb = tl * S + S - 1 < l1 ? tl * S + S - 1 : l1;
+            const int la = (tl << ls) > l0 ? tl << ls : l0;
+            const int lb = (tl << ls) + S - 1 < l1 ? (tl << ls) + S - 1 : l1;
             auto add = [&](int lo, int hi) {
-                int t1 = lo / S - wbase, t2 = hi / S - wbase;
+                int t1 = (lo >> ls) - wbase, t2 = (hi >> ls) - wbase;
                 if (t2 < 0 || t1 > 63) return;
                 t1 = t1 < 0 ? 0 : t1;
                 t2 = t2 > 63 ? 63 : t2;
