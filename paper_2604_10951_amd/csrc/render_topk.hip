@@ -47,6 +47,7 @@ struct SelShared {
     FsRecord rec[kSelBatch];
     uint32_t recid[kSelBatch];
     uint32_t sidx[kSelBatch];
+    int total;                     // pairs of the batch, -1 at the end (for the helping waves)
     int pre[kSelBatch];            // exclusive prefix of the entries' pair counts
     uint64_t pixels[kSelBatch];    // per entry: pixels of the block inside its box that are still walking
     uint32_t mask[64];             // per pixel: entries of the batch it accepts
@@ -97,40 +98,42 @@ FS_DEV void sel_sync() {
     }
 }
 
-// Block of a selection wave.  The first ceil(nblocks / WPG) workgroups
-// (dispatched first) take the long-list blocks, the i-th wave of them the
-// i-th long block; the others take every block in grid order, WPG
-// consecutive blocks per workgroup, and skip the long ones.  Returns -1 for
-// a wave without a block.
-template <int WPG>
-FS_DEV int64_t select_block_of(int64_t nblocks, const fs_camera* cams, int S, int sb2, const uint32_t* ranges,
-                               const uint32_t* lng, const uint32_t* counts) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t nwg = (nblocks + WPG - 1) / WPG;   // workgroups of each part
-    const int64_t wg = blockIdx.x;
-    if (wg >= nwg) {
+// Block of a selection wave.  The first nlong workgroups (dispatched first; 0:
+// no such part) take the long-list blocks: the i-th wave the i-th of them, or
+// with COOP one per workgroup, all its waves together.  The other workgroups
+// take every block in grid order, one per wave, and skip the long ones.  Returns
+// -1 for a wave without a block.
+template <int WPG, bool COOP>
+FS_DEV int64_t select_block_of(int64_t nblocks, uint32_t nlong, const fs_camera* cams, int S, int sb2,
+                               const uint32_t* ranges, const uint32_t* lng, const uint32_t* counts) {
+    const uint32_t wave = threadIdx.x >> 6, wg = blockIdx.x;
+    if (wg >= nlong) {
+        const int64_t nwg = (nblocks + WPG - 1) / WPG;
         const int64_t chunk = block_row_chunk(cams, S) / WPG;
-        const int64_t b = xcd_remap_chunked(wg - nwg, nwg, chunk > 0 ? chunk : 1) * WPG + wave;
+        const int64_t b = xcd_remap_chunked(wg - nlong, nwg, chunk > 0 ? chunk : 1) * WPG + wave;
         if (b >= nblocks) return -1;
         const int64_t t = b / sb2;
-        return ranges[2 * t + 1] - ranges[2 * t] > kSelLong ? -1 : b;
+        return nlong != 0u && ranges[2 * t + 1] - ranges[2 * t] > kSelLong ? -1 : b;
     }
-    const int64_t g = wg * WPG + wave;   // the long block of this wave
-    // the group holding long block g: running sum of the groups' counts
-    const int64_t ngroups = (nblocks + kSelGroup - 1) / kSelGroup;
+    const uint32_t i = COOP ? wg : wg * WPG + wave;   // the long block of this wave
+    // the group holding it: running sum of the groups' counts (taking the i /
+    // groups-th block of group i mod groups needs no sum but starts some long
+    // blocks later: 158 -> 163 us on the 300k-surfel 640x480 frame)
+    const uint32_t groups = (uint32_t)((nblocks + kSelGroup - 1) / kSelGroup);
+    const int lane = threadIdx.x & 63;
     uint32_t run = 0;
-    for (int64_t c0 = 0; c0 < ngroups; c0 += 64) {
-        const uint32_t c = c0 + lane < ngroups ? counts[c0 + lane] : 0u;
+    for (uint32_t c0 = 0; c0 < groups; c0 += 64) {
+        const uint32_t c = c0 + lane < groups ? counts[c0 + lane] : 0u;
         const uint32_t incl = __ockl_wfscan_add_u32(c, true);
-        const uint64_t past = __ballot((int64_t)(run + incl) > g);
+        const uint64_t past = __ballot(run + incl > i);
         if (past) {
             const int l = __builtin_ctzll(past);
             const uint32_t excl = run + __builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(c, l);
-            return lng[(c0 + l) * kSelGroup + (g - excl)];
+            return lng[(c0 + l) * kSelGroup + (i - excl)];
         }
         run += __builtin_amdgcn_readlane(incl, 63);
     }
-    return -1;   // fewer long blocks than g + 1
+    return -1;   // fewer long blocks than i + 1
 }
 
 // One wave writes the zero features of an 8x8 block (the part inside the
@@ -232,18 +235,26 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
                    int32_t* __restrict__ out_last, int32_t* __restrict__ out_idx, float* __restrict__ out_depth,
                    float* __restrict__ out_normal, uint64_t* __restrict__ counters,
                    const uint32_t* __restrict__ lng, const uint32_t* __restrict__ lcounts,
-                   float* __restrict__ out_feat, int C) {
+                   uint32_t nlong, float* __restrict__ out_feat, int C) {
     constexpr int BG = kSelBatch;
     constexpr int kQ = FS_RECORD_BYTES / 16;          // float4 per record
     constexpr int kRecSlots = (BG * kQ + 63) / 64;    // record float4 per lane
     static_assert(!BYW || KC > 0, "the by-weight lists live in LDS");
     static_assert(!(BYW && EXT), "no extended outputs for the by-weight selection");
     __shared__ SelShared<KC, BYW, EXT> sm_waves[WPG];
-    SelShared<KC, BYW, EXT>& sm = sm_waves[threadIdx.x >> 6];
+    // coop (by weight): a long-list block with the whole workgroup, whose first
+    // wave does everything but the pair evaluations, which all waves share: they
+    // are half of a batch's time, and the kernel lasts as long as its longest
+    // walks, which only T_stop ends (300k surfels, 640x480, K = 8: frame 259 ->
+    // 235 us; the first-K walks are short enough that the halved number of
+    // blocks in work costs more: 303 -> 315 us on the 1M-surfel 1280x720 frame)
+    const bool coop = BYW && WPG > 1 && blockIdx.x < nlong;   // uniform over the workgroup
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    SelShared<KC, BYW, EXT>& sm = sm_waves[coop ? 0 : wave];
     const int lane = threadIdx.x & 63;
     const int sb2 = (S / 8) * (S / 8);
-    const int64_t block = select_block_of<WPG>(nblocks, cams, S, sb2, ranges, lng, lcounts);
-    if (block < 0) return;   // uniform across the wave
+    const int64_t block = select_block_of<WPG, BYW>(nblocks, nlong, cams, S, sb2, ranges, lng, lcounts);
+    if (block < 0) return;   // uniform across the wave, and across the workgroup if coop
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
     if (!bp.valid) return;
     const fs_camera& cam = cams[bp.view];
@@ -290,6 +301,66 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
             if ((int64_t)rid[j] < num_records) pre[j] = reinterpret_cast<const float4*>(records + rid[j])[q];
         }
     };
+    // evaluates pairs first .. first + 64 kEvalPairs - 1, then every step-th such
+    // round, of the batch's `total` pairs.  kEvalPairs pairs per lane and round,
+    // as straight-line code (pairs past the end evaluate the last pair again and
+    // set no bit), so the dependent LDS reads and FP64 chains of the pairs overlap
+    auto evaluate = [&](int total, int first, int step) {
+        for (int k0 = first; k0 < total; k0 += step) {
+            int pe[kEvalPairs], pp[kEvalPairs];
+            bool hitp[kEvalPairs];
+#pragma unroll
+            for (int u = 0; u < kEvalPairs; ++u) {
+                const int k0u = k0 + u * 64 + lane;
+                const int k = k0u < total ? k0u : total - 1;
+                int e = 0;   // the entry owning pair k: last e with pre[e] <= k
+#pragma unroll
+                for (int h = BG / 2; h > 0; h >>= 1)
+                    if (sm.pre[e + h] <= k) e += h;
+                // the m-th set bit of the entry's pixel mask
+                int m = k - sm.pre[e];
+                uint64_t x = sm.pixels[e];
+                int p = 0;
+#pragma unroll
+                for (int sh = 32; sh >= 1; sh >>= 1) {
+                    const int c = __popcll(x & ((1ull << sh) - 1ull));
+                    if (m >= c) {
+                        m -= c;
+                        x >>= sh;
+                        p += sh;
+                    }
+                }
+                pe[u] = e;
+                pp[u] = p;
+            }
+#pragma unroll
+            for (int u = 0; u < kEvalPairs; ++u) {
+                const int e = pe[u], p = pp[u];
+                const int lx = p & 7, ly = p >> 3;
+                const FsRecord& r = sm.rec[e];
+                const double ddx = (double)(bp.x0 + lx - r.ax), ddy = (double)(bp.y0 + ly - r.ay);
+                FsResp rs = fs_response(r, ddx, ddy);
+                if constexpr (EXT)
+                    if (lowpass) fs_lowpass_d2(rs, ddx, ddy, sm.mu[e].x, sm.mu[e].y);
+                hitp[u] = k0 + u * 64 + lane < total && rs.d2 <= r.k2;
+            }
+#pragma unroll
+            for (int u = 0; u < kEvalPairs; ++u)
+                if (hitp[u]) atomicOr(&sm.mask[pp[u]], 1u << pe[u]);
+        }
+    };
+    if (coop && wave != 0) {
+        // the helpers' barriers pair with the first wave's: one before and one
+        // after every batch's evaluation, and a last one with the end mark
+        for (;;) {
+            __syncthreads();
+            const int total = sm.total;
+            if (total < 0) break;
+            evaluate(total, wave * 64 * kEvalPairs, WPG * 64 * kEvalPairs);
+            __syncthreads();
+        }
+        return;
+    }
     if (start < end) {
         uint32_t r0[kRecSlots];
         fetch_vals(start, r0);
@@ -368,50 +439,13 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
         }
         sm.mask[lane] = 0u;
         sel_sync<WPG>();
-        // kEvalPairs pairs per lane and round, as straight-line code (pairs
-        // past the end evaluate the last pair again and set no bit), so the
-        // dependent LDS reads and FP64 chains of the pairs overlap
-        for (int k0 = 0; k0 < total; k0 += 64 * kEvalPairs) {
-            int pe[kEvalPairs], pp[kEvalPairs];
-            bool hitp[kEvalPairs];
-#pragma unroll
-            for (int u = 0; u < kEvalPairs; ++u) {
-                const int k0u = k0 + u * 64 + lane;
-                const int k = k0u < total ? k0u : total - 1;
-                int e = 0;   // the entry owning pair k: last e with pre[e] <= k
-#pragma unroll
-                for (int step = BG / 2; step > 0; step >>= 1)
-                    if (sm.pre[e + step] <= k) e += step;
-                // the m-th set bit of the entry's pixel mask
-                int m = k - sm.pre[e];
-                uint64_t x = sm.pixels[e];
-                int p = 0;
-#pragma unroll
-                for (int sh = 32; sh >= 1; sh >>= 1) {
-                    const int c = __popcll(x & ((1ull << sh) - 1ull));
-                    if (m >= c) {
-                        m -= c;
-                        x >>= sh;
-                        p += sh;
-                    }
-                }
-                pe[u] = e;
-                pp[u] = p;
-            }
-#pragma unroll
-            for (int u = 0; u < kEvalPairs; ++u) {
-                const int e = pe[u], p = pp[u];
-                const int lx = p & 7, ly = p >> 3;
-                const FsRecord& r = sm.rec[e];
-                const double ddx = (double)(bp.x0 + lx - r.ax), ddy = (double)(bp.y0 + ly - r.ay);
-                FsResp rs = fs_response(r, ddx, ddy);
-                if constexpr (EXT)
-                    if (lowpass) fs_lowpass_d2(rs, ddx, ddy, sm.mu[e].x, sm.mu[e].y);
-                hitp[u] = k0 + u * 64 + lane < total && rs.d2 <= r.k2;
-            }
-#pragma unroll
-            for (int u = 0; u < kEvalPairs; ++u)
-                if (hitp[u]) atomicOr(&sm.mask[pp[u]], 1u << pe[u]);
+        if (coop) {
+            if (lane == 0) sm.total = total;
+            __syncthreads();   // the batch's records, pair counts and masks are in place
+            evaluate(total, 0, WPG * 64 * kEvalPairs);
+            __syncthreads();   // every wave's accepted pairs are in the masks
+        } else {
+            evaluate(total, 0, 64 * kEvalPairs);
         }
         sel_sync<WPG>();
         // (b) lane = pixel: front-to-back transmittance over its accepted
@@ -510,6 +544,10 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
             rowlist[nslots + (uint32_t)__popc(used & ((1u << lane) - 1u))] = sm.sidx[lane];
         nslots += (uint32_t)__popc(used);
         if (__all(done)) break;
+    }
+    if (coop) {   // release the helpers
+        if (lane == 0) sm.total = -1;
+        __syncthreads();
     }
 
     if constexpr (BYW) {
@@ -1040,14 +1078,18 @@ hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, 
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(select_long_kernel, dim3((unsigned)((nblocks + kSelGroup - 1) / kSelGroup)), dim3(kSelGroup), 0,
                        s, ranges, sb * sb, nblocks, ws.sel_long, ws.sel_counts);
+    // (a launch holds fewer than 2^32 threads: without the long part beyond that)
+    const int64_t long_waves = (nblocks + kSelGroup - 1) / kSelGroup * kSelGroup;
+    const int64_t long_wgs = o.topk_mode == FS_TOPK_WEIGHT ? long_waves : long_waves / 2;
+    const uint32_t nlong = (long_wgs + nblocks / 2 + 1) * 128 < (int64_t(1) << 32) ? (uint32_t)long_wgs : 0u;
 #define FS_SEL_LAUNCH(WPG)                                                                                      \
-    hipLaunchKernelGGL(FS_SEL_KERN(WPG), dim3((unsigned)(2 * ((nblocks + WPG - 1) / WPG))), dim3(64 * WPG), 0, s,  \
+    hipLaunchKernelGGL(FS_SEL_KERN(WPG), dim3((unsigned)(nlong + (nblocks + WPG - 1) / WPG)), dim3(64 * WPG), 0, s,   \
                        records, keys, vals, ranges, (uint32_t)n, n * num_views, cams, num_views, o.tile, o, nblocks,  \
                        ws.topk_pairs, ws.topk_rows, ws.topk_nrows, out_T, out_n, out_last, out_idx, out_depth,        \
-                       out_normal, counters, ws.sel_long, ws.sel_counts, out_feat, C)
-    // two selection waves per workgroup (one block each): measured on the
-    // 1280x720 C = 128 frame, Top-K render 0.1887 / 0.1862 / 0.1951 ms for
-    // one, two and four waves per workgroup
+                       out_normal, counters, ws.sel_long, ws.sel_counts, nlong, out_feat, C)
+    // two selection waves per workgroup (one block each, or one long-list block
+    // together): measured on the 1280x720 C = 128 frame with a block per wave,
+    // Top-K render 0.1887 / 0.1862 / 0.1951 ms for one, two and four waves
     FS_SEL_LAUNCH(2);
 #undef FS_SEL_LAUNCH
 #undef FS_SEL_KERN
