@@ -1076,12 +1076,18 @@ hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, 
     if (ws.sel_long == nullptr || ws.sel_counts == nullptr || nblocks > ws.render_max_blocks ||
         2 * nblocks >= (int64_t(1) << 31))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(select_long_kernel, dim3((unsigned)((nblocks + kSelGroup - 1) / kSelGroup)), dim3(kSelGroup), 0,
-                       s, ranges, sb * sb, nblocks, ws.sel_long, ws.sel_counts);
     // (a launch holds fewer than 2^32 threads: without the long part beyond that)
     const int64_t long_waves = (nblocks + kSelGroup - 1) / kSelGroup * kSelGroup;
     const int64_t long_wgs = o.topk_mode == FS_TOPK_WEIGHT ? long_waves : long_waves / 2;
-    const uint32_t nlong = (long_wgs + nblocks / 2 + 1) * 128 < (int64_t(1) << 32) ? (uint32_t)long_wgs : 0u;
+    uint32_t nlong = (long_wgs + nblocks / 2 + 1) * 128 < (int64_t(1) << 32) ? (uint32_t)long_wgs : 0u;
+    // first-K frames whose blocks are all in flight at once (sixteen waves on each
+    // of 256 CUs) need no order: without the list launch and the waves that find
+    // no long block a label frame of 2,267 surfels, 223x169, takes 75.8 us
+    // instead of 78.8
+    if (o.topk_mode != FS_TOPK_WEIGHT && nblocks <= 4096) nlong = 0u;
+    if (nlong != 0u)
+        hipLaunchKernelGGL(select_long_kernel, dim3((unsigned)((nblocks + kSelGroup - 1) / kSelGroup)), dim3(kSelGroup),
+                           0, s, ranges, sb * sb, nblocks, ws.sel_long, ws.sel_counts);
 #define FS_SEL_LAUNCH(WPG)                                                                                      \
     hipLaunchKernelGGL(FS_SEL_KERN(WPG), dim3((unsigned)(nlong + (nblocks + WPG - 1) / WPG)), dim3(64 * WPG), 0, s,   \
                        records, keys, vals, ranges, (uint32_t)n, n * num_views, cams, num_views, o.tile, o, nblocks,  \
