@@ -582,7 +582,7 @@ def main():
         "render_counters": {"topk": top["counters"], "full": full["counters"]},
         "roofline": {"kernel": ("render forward, Top-K: topk_select_kernel + topk_gather_lds_kernel (one "
                                 "fs_render_forward call)" if args.schedule == "split" else
-                                "render_fwd_kernel (Top-K)"),
+                                "render_wide_kernel (Top-K)"),
                      "bound": "hbm", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic(args.schedule) if args.tile == TILE else None,

@@ -11,7 +11,7 @@
 // (12 B per entry), which costs far less than the walk it saves: one workgroup
 // per 16x16 pixels, walking every entry of the tile, took 1.24 ms for the
 // 300k-surfel, 640x480, C = 48 full-blend frame (16x16 tiles) against 0.27 ms
-// here.  A block exits as soon as every pixel has stopped (T_stop, or K blended
+// with the queue alone and 0.17 ms with all that follows.  A block exits as soon as every pixel has stopped (T_stop, or K blended
 // surfels), which is where Top-K saves work.  Feature images are written
 // pixel-major (channels contiguous).
 #include <type_traits>
