@@ -120,8 +120,8 @@ template <int CPT, typename FT, bool FILTER>
 __global__ void __launch_bounds__(kBwdThreads)
 render_bwd_kernel(const FsRecord* __restrict__ records, const uint32_t* __restrict__ vals,
                   const uint32_t* __restrict__ ranges, const FT* __restrict__ feats, int C, int64_t n,
-                  int64_t num_records, const fs_camera* __restrict__ cams, int num_views, int S, fs_opts o,
-                  const float* __restrict__ out_T, const int32_t* __restrict__ out_last,
+                  int64_t num_records, const fs_camera* __restrict__ cams, int num_views, int S, int64_t nblocks,
+                  fs_opts o, const float* __restrict__ out_T, const int32_t* __restrict__ out_last,
                   const float* __restrict__ grad_feat, float* __restrict__ grad_records,
                   float* __restrict__ grad_feats) {
     constexpr int NT = kBwdThreads, NW = NT / 64;
@@ -135,7 +135,10 @@ render_bwd_kernel(const FsRecord* __restrict__ records, const uint32_t* __restri
     // grid row 0 (dispatched first) takes the blocks with long lists, row 1 the
     // others; the XCDs take one tile row of blocks each in turn
     const bool second = blockIdx.y != 0;
-    const int64_t block = xcd_remap_chunked(blockIdx.x, gridDim.x, block_row_chunk(cams, S));
+    // (a launch row holds fewer than 2^32 threads; larger frames take several)
+    const int64_t g = blockIdx.x + (int64_t)gridDim.x * blockIdx.z;
+    if (g >= nblocks) return;
+    const int64_t block = xcd_remap_chunked(g, nblocks, block_row_chunk(cams, S));
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
     if (!bp.valid) return;
     const uint32_t start = ranges[2 * bp.tile], end = ranges[2 * bp.tile + 1];
@@ -779,9 +782,11 @@ hipError_t launch_bwd(const FsRecord* records, const uint32_t* vals, const uint3
     const int64_t blocks = total_tiles * sb * sb;
     if (blocks >= (int64_t(1) << 32)) return hipErrorInvalidValue;
     const auto kern = sb > 1 ? render_bwd_kernel<CPT, FT, true> : render_bwd_kernel<CPT, FT, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, 2), dim3(kBwdThreads), 0, s, records, vals, ranges,
-                       static_cast<const FT*>(feats), C, n, n * num_views, cams, num_views, o.tile, o, out_T, out_last,
-                       grad_feat, grad_records, grad_feats);
+    const int64_t most = int64_t(1) << 23, row = blocks < most ? blocks : most;
+    hipLaunchKernelGGL(kern, dim3((unsigned)row, 2, (unsigned)((blocks + row - 1) / row)), dim3(kBwdThreads), 0, s,
+                       records, vals, ranges,
+                       static_cast<const FT*>(feats), C, n, n * num_views, cams, num_views, o.tile, blocks, o, out_T,
+                       out_last, grad_feat, grad_records, grad_feats);
     return hipGetLastError();
 }
 

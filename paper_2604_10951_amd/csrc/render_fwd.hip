@@ -539,7 +539,10 @@ render_wide_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
     if (order == nullptr) {
         // the XCDs take one tile row of blocks each in turn: neighbouring
         // blocks share an L2 and dense regions are spread over all XCDs
-        const int64_t blk = xcd_remap_chunked(blockIdx.x, gridDim.x, block_row_chunk(cams, S));
+        // (a launch row holds fewer than 2^32 threads; larger frames take several)
+        const int64_t g = blockIdx.x + (int64_t)gridDim.x * blockIdx.z;
+        if (g >= nblocks) return;
+        const int64_t blk = xcd_remap_chunked(g, nblocks, block_row_chunk(cams, S));
         render_block_wide<NVT, FT, NW, BG, VEC, EXT, FILTER>(blk, sm, records, keys, vals, ranges, feats, C, n, num_records,
                                                      cams, num_views, S, o, out_feat, out_T, out_n, out_last,
                                                      out_idx, out_depth, out_normal, counters);
@@ -632,6 +635,8 @@ order_place_kernel(const uint32_t* __restrict__ ranges, int sb2, uint32_t nblock
     }
 }
 
+constexpr int64_t kMaxRow = int64_t(1) << 23;   // workgroups of 256 threads in one row of a launch
+
 int device_cus() {
     static int cus = 0;
     if (cus == 0) {
@@ -678,10 +683,12 @@ hipError_t launch_wide(const FsRecord* records, const uint64_t* keys, const uint
                            ws.render_ticket, nb);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)chunks), dim3(NW * 64), 0, s, records, keys, vals,
+    const int64_t row = blocks < kMaxRow ? blocks : kMaxRow;
+    hipLaunchKernelGGL(kern, dim3((unsigned)row, (unsigned)chunks, (unsigned)((blocks + row - 1) / row)), dim3(NW * 64),
+                       0, s, records, keys, vals,
                        ranges, static_cast<const FT*>(feats), C, n, n * num_views, cams, num_views, o.tile, o,
                        out_feat, out_T, out_n, out_last, out_idx, out_depth, out_normal, counters,
-                       (const uint32_t*)nullptr, (uint32_t*)nullptr, 0u);
+                       (const uint32_t*)nullptr, (uint32_t*)nullptr, (uint32_t)blocks);
     return hipGetLastError();
 }
 
