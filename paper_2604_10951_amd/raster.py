@@ -111,8 +111,6 @@ class Rasterizer:
 
     # -- buffers ------------------------------------------------------------
     def _ensure(self, n: int, capacity: int):
-        if n == self._n and capacity <= self.capacity and "ws" in self._bufs:
-            return
         if n != self._n:
             V = self.num_views
             self._bufs["records"] = torch.empty(V * n * L.FS_RECORD_BYTES, dtype=torch.uint8, device=self.device)
@@ -126,6 +124,7 @@ class Rasterizer:
             self.capacity = max(capacity, self.capacity, 1024)
             self._bufs["keys"] = torch.empty(self.capacity, dtype=torch.int64, device=self.device)
             self._bufs["vals"] = torch.empty(self.capacity, dtype=torch.int32, device=self.device)
+        # asked anew for every frame: the options decide it too, and they can change between frames
         ws = self.lib.fs_workspace_bytes(n, self.num_views, self.total_tiles, self.capacity, ctypes.byref(self.opts))
         if "ws" not in self._bufs or self._bufs["ws"].numel() < ws:
             self._bufs["ws"] = torch.empty(max(ws, 256), dtype=torch.uint8, device=self.device)
