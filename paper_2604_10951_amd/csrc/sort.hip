@@ -462,19 +462,24 @@ FS_DEV bool sort_run_buckets(uint64_t* s, BucketShared& b, const uint2* __restri
         s[b.part[q] + atomicAdd(&b.fill[q], 1u)] = composite(x);
     });
     __syncthreads();
-    auto place_of = [&](const uint2& x) {
-        const int q = part_of(x.x);
+    // the place of the entry in slot i of s: equal entries (the caller's own
+    // lists may repeat a pair) go by their slots, so that no two share a place
+    auto place_of = [&](int i, uint64_t v) {
+        const int q = part_of((uint32_t)(v >> 32));
         const uint32_t p0 = b.part[q], p1 = b.part[q + 1];
-        const uint64_t v = composite(x);
         uint32_t r = p0;
-        for (uint32_t p = p0; p < p1; ++p) r += s[p] < v ? 1u : 0u;
+        for (uint32_t p = p0; p < p1; ++p) {
+            const uint64_t y = s[p];
+            r += y < v || (y == v && p < (uint32_t)i) ? 1u : 0u;
+        }
         return r;
     };
     if constexpr (HELD) {
-        const uint32_t r0 = tid < n ? place_of(x0) : 0u, r1 = i1 < n ? place_of(x1) : 0u;
+        const uint64_t v0 = tid < n ? s[tid] : 0ull, v1 = i1 < n ? s[i1] : 0ull;
+        const uint32_t r0 = tid < n ? place_of(tid, v0) : 0u, r1 = i1 < n ? place_of(i1, v1) : 0u;
         __syncthreads();
-        if (tid < n) s[r0] = composite(x0);
-        if (i1 < n) s[r1] = composite(x1);
+        if (tid < n) s[r0] = v0;
+        if (i1 < n) s[r1] = v1;
         __syncthreads();
         for (int i = tid; i < n; i += kLongThreads) {
             const uint64_t v = s[i];
@@ -482,11 +487,12 @@ FS_DEV bool sort_run_buckets(uint64_t* s, BucketShared& b, const uint2* __restri
             vals[start + i] = (uint32_t)v;
         }
     } else {
-        each([&](const uint2& x) {
-            const uint32_t r = place_of(x);
-            keys[start + r] = (tile << 32) | x.x;
-            vals[start + r] = x.y;
-        });
+        for (int i = tid; i < n; i += kLongThreads) {
+            const uint64_t v = s[i];
+            const uint32_t r = place_of(i, v);
+            keys[start + r] = (tile << 32) | (v >> 32);
+            vals[start + r] = (uint32_t)v;
+        }
     }
     return true;
 }
