@@ -273,9 +273,12 @@ fs_status fs_sort(uint64_t* keys, uint32_t* vals, int64_t pair_capacity, const i
  *              Depth and normal follow the same blend (and Top-K selection)
  *              as the features; FS_ERR_UNSUPPORTED with FS_TOPK_WEIGHT.
  *   counters   optional in/out, 4 uint64 added to: [0] list entries walked
- *              (over all 8x8 render blocks), [1] feature rows the
- *              blocks need (one per block and entry blended by any of its
- *              pixels), [2] blended (pixel, surfel) pairs, [3] blocks run
+ *              (over all blocks), [1] feature rows the blocks need (one per
+ *              block and entry blended by any of its pixels), [2] blended
+ *              (pixel, surfel) pairs, [3] blocks run; a block is 8x8 pixels
+ *              with 8x8 tiles and in the split schedule, 16x16 otherwise,
+ *              and walks its tile's list in whole batches until all its
+ *              pixels have stopped
  *   keys       the sorted keys of fs_sort, read only for out_depth (else NULL)
  */
 fs_status fs_render_forward(const void* records, const uint64_t* keys, const uint32_t* vals,

@@ -161,7 +161,7 @@ FS_DEV void render_block_wide(int64_t block, WideShared<NVT, FT, NW, BG, EXT, FI
         for (int i = 0; i < kVE; ++i) acc[v][i] = 0.f;
     const double t_stop = o.t_stop;
     const float neg_half_log2e = -0.72134752044448170f;   // -log2(e) / 2
-    uint32_t walked = FILTER ? end - start : 0u, fetched = 0;
+    uint32_t walked = 0, fetched = 0;   // 8x8 tiles (count_walk_kernel counts for larger ones)
 
     // records of batch i + 1 and list values of batch i + 2 are in flight
     // while batch i is processed
@@ -407,10 +407,10 @@ FS_DEV void render_block_wide(int64_t block, WideShared<NVT, FT, NW, BG, EXT, FI
                 sm.used = wused;
                 sm.active = wactive ? 1u : 0u;
             }
-            // entries walked: to the end of the list once the queue runs dry
-            walked = !FILTER ? walked + (uint32_t)nb
-                             : (qt - qh == (uint32_t)nb && cp >= end ? end : pos_of(nb - 1) + 1u) - start;
-            fetched += (uint32_t)__popc(wused);
+            if constexpr (!FILTER) {
+                walked += (uint32_t)nb;
+                fetched += (uint32_t)__popc(wused);
+            }
         }
         if (pbuf >= 0) accumulate(pbuf);
         __syncthreads();   // C: the walk is done, the previous batch's rows are no longer read
@@ -459,7 +459,7 @@ FS_DEV void render_block_wide(int64_t block, WideShared<NVT, FT, NW, BG, EXT, FI
         accumulate(pbuf);
     }
 
-    if (counters != nullptr && chunk == 0 && wave == walker) {
+    if (!FILTER && counters != nullptr && chunk == 0 && wave == walker) {
         int c = cnt;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) c += __shfl_xor(c, d, 64);
@@ -566,6 +566,107 @@ render_wide_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
         __syncthreads();   // every wave is done with the item; the next one is known
         it = (ahead + sm.item) * nq + q;
         __syncthreads();
+    }
+}
+
+// The counters of a render with 16x16 or 32x32 tiles.  They are defined over
+// 16x16 pixel blocks that walk their tile's whole list a batch of bg entries at a
+// time until every pixel has stopped, and not over the blocks the render works
+// in, so a pass of its own counts them, run only when they are asked for: one
+// thread per pixel (a wave per 8x8 of them), with the render's response, stop and
+// Top-K tests.
+__global__ void __launch_bounds__(256)
+count_walk_kernel(const FsRecord* __restrict__ records, const uint32_t* __restrict__ vals,
+                  const uint32_t* __restrict__ ranges, int64_t num_records, const fs_camera* __restrict__ cams,
+                  int num_views, int S, fs_opts o, int bg, int64_t nblocks, uint64_t* __restrict__ counters) {
+    constexpr int kQ = FS_RECORD_BYTES / 16;
+    __shared__ FsRecord s_rec[32];
+    __shared__ double2 s_mu[32];
+    __shared__ uint32_t s_used[4], s_active[4];
+    __shared__ uint64_t s_pairs[4];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int K = o.topk;
+    const double t_stop = o.t_stop;
+    uint64_t walked = 0, rows = 0, blocks = 0, blended = 0;   // blended: this thread's pixels; the others uniform
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        const BlockPos bp = locate_block(b, S, 16, cams, num_views);
+        if (!bp.valid) continue;   // uniform across the workgroup, as every exit below
+        const fs_camera& cam = cams[bp.view];
+        const int x0 = bp.x0 + (wave & 1) * 8, y0 = bp.y0 + (wave >> 1) * 8;
+        const int px = x0 + (lane & 7), py = y0 + (lane >> 3);
+        const uint32_t start = ranges[2 * bp.tile], end = ranges[2 * bp.tile + 1];
+        double T = 1.0;
+        int cnt = 0;
+        bool done = px >= cam.width || py >= cam.height;
+        ++blocks;
+        // record float4 pq of entry pe; the next batch's records and the list
+        // values after those are in flight while a batch is walked
+        const int pe = tid / kQ, pq = tid - pe * kQ;
+        auto val_at = [&](uint32_t p) { return pe < bg && p + (uint32_t)pe < end ? vals[p + pe] : 0xffffffffu; };
+        auto record_of = [&](uint32_t rid) {
+            float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
+            if ((int64_t)rid < num_records)
+                v4 = reinterpret_cast<const float4*>(records + rid)[pq];
+            else if (pq == 5)   // past the list (never in a well-formed one)
+                v4.z = __int_as_float(1);   // empty box
+            return v4;
+        };
+        float4 pre = record_of(val_at(start));
+        uint32_t nxt = val_at(start + (uint32_t)bg);
+        for (uint32_t b0 = start; b0 < end; b0 += (uint32_t)bg) {
+            const int nb = (int)(end - b0 < (uint32_t)bg ? end - b0 : (uint32_t)bg);
+            __syncthreads();   // the previous batch is no longer read
+            if (pe < nb) reinterpret_cast<float4*>(&s_rec[pe])[pq] = pre;
+            pre = record_of(nxt);
+            nxt = val_at(b0 + 2u * (uint32_t)bg);
+            __syncthreads();
+            if (o.lowpass != 0) {
+                if (tid < nb) fs_record_centre(s_rec[tid], s_mu[tid].x, s_mu[tid].y);
+                __syncthreads();
+            }
+            uint32_t mask = 0u;
+            for (int e = 0; e < nb; ++e) {
+                const FsRecord& r = s_rec[e];
+                if (r.x1 < x0 || r.x0 > x0 + 7 || r.y1 < y0 || r.y0 > y0 + 7) continue;
+                if (done || px < r.x0 || px > r.x1 || py < r.y0 || py > r.y1) continue;
+                const double dx = (double)(px - r.ax), dy = (double)(py - r.ay);
+                FsResp rs = fs_response(r, dx, dy);
+                if (o.lowpass != 0) fs_lowpass_d2(rs, dx, dy, s_mu[e].x, s_mu[e].y);
+                if (!(rs.d2 <= r.k2)) continue;
+                const float G = __builtin_amdgcn_exp2f(-0.72134752044448170f * (float)rs.d2);
+                const double Tn = T * (1.0 - (double)fminf(o.alpha_max, r.o * G));
+                if (Tn < t_stop) {
+                    done = true;
+                } else {
+                    T = Tn;
+                    mask |= 1u << e;
+                    ++cnt;
+                    if (K > 0 && cnt == K) done = true;
+                }
+            }
+            const uint32_t used = wave_or(mask);
+            const bool active = !__all(done);
+            if (lane == 0) {
+                s_used[wave] = used;
+                s_active[wave] = active ? 1u : 0u;
+            }
+            __syncthreads();
+            walked += (uint64_t)nb;
+            rows += (uint64_t)__popc(s_used[0] | s_used[1] | s_used[2] | s_used[3]);
+            if ((s_active[0] | s_active[1] | s_active[2] | s_active[3]) == 0u) break;
+        }
+        blended += (uint64_t)cnt;
+        __syncthreads();   // the last batch is no longer read
+    }
+    const uint64_t sum = __ockl_wfred_add_u64(blended);
+    if (lane == 0) s_pairs[wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        const uint64_t pairs = s_pairs[0] + s_pairs[1] + s_pairs[2] + s_pairs[3];
+        atomicAdd((unsigned long long*)&counters[0], (unsigned long long)walked);
+        atomicAdd((unsigned long long*)&counters[1], (unsigned long long)rows);
+        atomicAdd((unsigned long long*)&counters[2], (unsigned long long)pairs);
+        atomicAdd((unsigned long long*)&counters[3], (unsigned long long)blocks);
     }
 }
 
@@ -741,6 +842,17 @@ hipError_t fs_launch_render_forward(const FsRecord* records, const uint64_t* key
                                     const FsWorkspace& ws, hipStream_t s) {
     if (total_tiles == 0) return hipSuccess;
     const bool bf16 = o.feat_dtype == FS_FEAT_BF16;
+    if (counters != nullptr && o.tile > 8) {
+        const bool ext = o.lowpass != 0 || out_depth != nullptr || out_normal != nullptr;
+        const int64_t blocks = total_tiles * (o.tile / 16) * (o.tile / 16);
+        // (the counters' atomics are serialised per address, about 50 ns each)
+        const int64_t grid = blocks < 2048 ? blocks : 2048;
+        hipLaunchKernelGGL(count_walk_kernel, dim3((unsigned)grid), dim3(256), 0, s, records, vals, ranges,
+                           n * num_views, cams, num_views, o.tile, o, o.batch == 16 && !ext ? 16 : 32, blocks, counters);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        counters = nullptr;
+    }
 #define FS_WAVES(NVTv, FTv)                                                                                          \
     return launch_waves<NVTv, FTv>(records, keys, vals, ranges, feats, C, n, cams, num_views, total_tiles, o,      \
                                    out_feat, out_T, out_n, out_last, out_idx, out_depth, out_normal, counters, ws, s)
