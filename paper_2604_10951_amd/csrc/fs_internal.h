@@ -919,7 +919,8 @@ template <int LOGE>
 FS_DEV void wave_network(uint64_t (&x)[1 << LOGE]) {
     constexpr int E = 1 << LOGE;
     constexpr int LOGN = 6 + LOGE;
-    const int lane = (int)threadIdx.x & 63;
+    int lane = (int)threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // keeps the lane masks of every stage from being hoisted out of a caller's loop and spilled
 #pragma unroll
     for (int lk = 1; lk <= LOGN; ++lk) {
         const int k = 1 << lk;

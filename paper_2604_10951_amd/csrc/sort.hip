@@ -14,9 +14,9 @@
 //   2. a sort of every tile's run by (depth key, record), as 64-bit composite
 //      keys: runs of up to kWaveCap entries by one wave each (bitonic network
 //      in the wave's registers), up to kLargeCap by a workgroup (distributed
-//      over equal parts of their depth range in 64 KB of LDS; a bitonic network
-//      there if the depths are bunched), longer runs by a stable one-workgroup
-//      LSD radix sort through global memory.  The scan that writes the ranges also lists the long runs.
+//      in 64 KB of LDS over parts cut by samples of the run), longer runs by a stable
+//      one-workgroup LSD radix sort through global memory.  The scan that writes the ranges
+//      also lists the long runs.
 // Every launch is sized from the capacity, not from the device-side pair
 // count, so the sequence can be captured in a graph.
 #include "fs_internal.h"
@@ -27,6 +27,7 @@ constexpr int kThreads = 256;
 constexpr int kWaveCap = 256;     // entries per run sorted by one wave (4 per lane, in registers): short +
                                   // long kernels 26.2 us on the 1M-surfel 1280x720 frame, 30.0 with 512,
                                   // 26.5 with 128; sixteen views 163, 162 and 169
+constexpr int kMidCap = 512;      // entries per run sorted by a quarter of a long-run workgroup
 constexpr int kLargeCap = 8192;   // entries per run sorted in LDS by a workgroup (64 KB)
 constexpr int kLdsTiles = 16384;  // tile counts kept in LDS by the count and scatter kernels
 constexpr int kChunk = 8192;      // pairs per workgroup in the count and scatter kernels
@@ -333,166 +334,185 @@ FS_DEV void sort_run_wave(const uint2* __restrict__ in, uint64_t tile, uint32_t 
     }
 }
 
-// Bitonic sort of s[0, n2) (n2 a power of two, padding = ~0) by the workgroup.
-template <int NT>
-FS_DEV void bitonic_lds(uint64_t* s, int n2) {
-    for (int k = 2; k <= n2; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < (n2 >> 1); i += NT) {
-                const int a = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-                const int b = a + j;
-                const bool up = (a & k) == 0;
-                const uint64_t x = s[a], y = s[b];
-                if ((x > y) == up) {
-                    s[a] = y;
-                    s[b] = x;
-                }
-            }
-            __syncthreads();
-        }
-    }
+// The thread's index, opaque to the compiler: a workgroup sorts its long runs in a
+// loop with a form for each length, and the addresses and masks of all forms would
+// be hoisted out of that loop and spilled.
+FS_DEV int own_thread() {
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
 }
 
-FS_DEV int next_pow2(int n) {
-    int p = 1;
-    while (p < n) p <<= 1;
-    return p;
-}
-
-// Sort one run of 2 <= n <= capacity of s entries in LDS and write the final
-// keys and values.
-template <int NT>
-FS_DEV void sort_run_lds(uint64_t* s, const uint2* __restrict__ in, uint64_t tile, uint32_t start, int n,
-                         uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    const int n2 = next_pow2(n);
-    for (int i = threadIdx.x; i < n2; i += NT) s[i] = i < n ? composite(in[start + i]) : ~0ull;
-    __syncthreads();
-    bitonic_lds<NT>(s, n2);
-    for (int i = threadIdx.x; i < n; i += NT) {
-        const uint64_t c = s[i];
-        keys[start + i] = (tile << 32) | (c >> 32);
-        vals[start + i] = (uint32_t)c;
-    }
-}
-
-// Sort of one run of n <= kLargeCap entries by the workgroup in one
-// distribution step: the depth keys' range is cut into kBuckets equal parts (a
-// monotone map), entries go to LDS grouped by part, and an entry's place inside
-// its part is the number of the part's entries before it, counted directly.  A
-// run's depths spread over the parts (a few entries each), so an entry costs an
-// LDS atomic or two and a few reads, where the sorted chunks and merges of
-// before cost it 20 to 45 exchanges and 20 dependent reads: long runs of the
-// sixteen-view frame 217 -> 112 us, of the 1M-surfel 1280x720 frame 26 -> 11.5 (runs over 512).
+// Sort of one run of n <= G E entries by a group of G threads in one distribution
+// step: entries go to LDS grouped by part, the parts in order, and an entry's
+// place inside its part is the number of the part's entries before it, counted
+// directly.  64 samples (128 for the longest runs) tell how to cut: equal parts of
+// the depth range where the samples spread over it; where they crowd, the
+// intervals between the sorted samples, each cut into equal parts of its range of
+// (depth, record).  A part then holds a few entries however the depths are spread
+// (equal parts alone put a camera-facing wall in front of a far background into one
+// part; sorting 3,600 runs of 1,000 such entries, with the 20 us that restore the
+// pairs, took 237 us with a network for such runs, 222 with chunks sorted by waves
+// and merged, 146 this way; normally distributed depths 127, 221 and 120, and 900
+// runs of 8,000 such entries 280, 373 and 177).
 // Returns false, having written nothing, if a part holds more than kPartMax
-// entries (depths bunched beyond the map's resolution): uniform over the
-// workgroup.  Up to two entries per thread stay in registers (HELD); longer
-// runs are read again from memory in every phase.
-constexpr int kBuckets = kLongThreads;
-constexpr uint32_t kPartMax = 64;
-struct BucketShared {
-    uint32_t part[kBuckets + 1];   // entries, then first place, of every part
-    uint32_t fill[kBuckets];       // entries placed so far
-    uint32_t red[2 * (kLongThreads / 64)];
+// entries (a pair repeated that often): uniform over the group.
+// All threads of the workgroup call it together (barriers); n = 0: nothing to do.
+constexpr uint32_t kPartMax = 1024;
+template <int G, int P>
+struct PartShared {
+    uint64_t split[129];           // crowded: interval k is [split[k], split[k + 1]); entries outside go to its ends
+    uint32_t part[P];              // entries, then next place, in the end the end of every part
+    uint32_t red[2 * (G / 64)];
+    uint32_t cell[512];            // samples in each 512th of the range
+    uint32_t lo, even;
+    float scale;
 };
-template <bool HELD>
-FS_DEV bool sort_run_buckets(uint64_t* s, BucketShared& b, const uint2* __restrict__ in, uint64_t tile, uint32_t start,
-                             int n, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    constexpr int kWaves = kLongThreads / 64;
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int i1 = tid + kLongThreads;
-    uint2 x0 = make_uint2(0u, 0u), x1 = make_uint2(0u, 0u);
-    uint32_t lo = ~0u, hi = 0u;
-    // f(entry) for every entry of this thread
-    auto each = [&](auto&& f) {
-        if constexpr (HELD) {
-            if (tid < n) f(x0);
-            if (i1 < n) f(x1);
-        } else {
-            for (int i = tid; i < n; i += kLongThreads) f(in[start + i]);
-        }
+// E = 0: runs of up to kLargeCap entries, read again in every phase (held in
+// registers, 8 per thread, they spill).
+template <int G, int E, int P>
+FS_DEV bool sort_run_parts(uint64_t* s, PartShared<G, P>& b, const uint2* __restrict__ in, uint64_t tile, uint32_t start,
+                           int n, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    constexpr int kWaves = G / 64, kLogS = E > 0 ? 0 : 1, kS = 64 << kLogS, kParts = E == 1 ? P / 2 : P, kSub = kParts / kS;
+    // samples in one 512th of the range beyond which they crowd: normal, uniform
+    // and exponential depths give 2 to 5, forty equal planes 5 to 8
+    constexpr uint32_t kCrowd = E > 0 ? 4u : 6u;
+    constexpr int kPer = kParts / G;   // parts per thread
+    static_assert(kPer * G == kParts, "whole parts per thread");
+    const int tid = own_thread() & (G - 1), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto fence = [] {   // one wave's LDS accesses complete in order
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     };
-    if constexpr (HELD) {
-        if (tid < n) x0 = in[start + tid];
-        if (i1 < n) x1 = in[start + i1];
-    }
-    each([&](const uint2& x) {
-        lo = x.x < lo ? x.x : lo;
-        hi = x.x > hi ? x.x : hi;
-    });
-    lo = __ockl_wfred_min_u32(lo);
-    hi = __ockl_wfred_max_u32(hi);
-    if (lane == 0) {
-        b.red[wave] = lo;
-        b.red[kWaves + wave] = hi;
-    }
-    b.part[tid] = 0u;
-    b.fill[tid] = 0u;
-    __syncthreads();
+    uint64_t v[E > 0 ? E : 1];   // this thread's entries, and their parts
+    uint32_t at[E > 0 ? E : 1];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        lo = b.red[w] < lo ? b.red[w] : lo;
-        hi = b.red[kWaves + w] > hi ? b.red[kWaves + w] : hi;
+    for (int e = 0; e < E; ++e) v[e] = tid + e * G < n ? composite(in[start + tid + e * G]) : 0ull;
+    if (wave == kWaves - 1 && n > 0) {   // entries arrive in no particular order: evenly spaced ones are the samples
+        uint64_t x[1 << kLogS];
+        uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+        for (int j = 0; j < 1 << kLogS; ++j) {
+            x[j] = composite(in[start + (uint32_t)(((lane << kLogS) + j) * n / kS)]);
+            lo = min(lo, (uint32_t)(x[j] >> 32));
+            hi = max(hi, (uint32_t)(x[j] >> 32));
+        }
+        lo = __ockl_wfred_min_u32(lo);
+        hi = __ockl_wfred_max_u32(hi);
+        const uint32_t margin = (hi - lo) >> 2;   // for the entries beyond the outermost samples
+        lo = lo > margin ? lo - margin : 0u;
+        const float scale = (float)kParts / ((float)(hi - lo) + (float)margin + 1.f);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b.cell[lane + 64 * j] = 0u;
+        fence();
+        const float cells = scale * (512.f / (float)kParts);
+#pragma unroll
+        for (int j = 0; j < 1 << kLogS; ++j)
+            atomicAdd(&b.cell[min(511, (int)((float)((uint32_t)(x[j] >> 32) - lo) * cells))], 1u);
+        fence();
+        uint32_t crowd = 0u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) crowd = max(crowd, b.cell[lane + 64 * j]);
+        const bool even = __ockl_wfred_max_u32(crowd) <= kCrowd;
+        if (!even) {
+            wave_network<kLogS>(x);
+#pragma unroll
+            for (int j = 0; j < 1 << kLogS; ++j) b.split[(lane << kLogS) + j] = x[j];
+            fence();
+            if (lane == 0) {
+                const uint64_t s0 = b.split[0], s1 = b.split[kS - 1];
+                const uint64_t below = 2u * (b.split[2] - s0), above = 2u * (s1 - b.split[kS - 3]) + 1u;
+                b.split[0] = s0 > below ? s0 - below : 0ull;
+                b.split[kS] = ~0ull - s1 > above ? s1 + above : ~0ull;
+            }
+        }
+        if (lane == 0) {
+            b.lo = lo;
+            b.scale = scale;
+            b.even = even ? 1u : 0u;
+        }
     }
-    const float scale = hi > lo ? (float)(kBuckets - 1) / (float)(hi - lo) : 0.f;
-    auto part_of = [&](uint32_t d) {
-        const int q = (int)((float)(d - lo) * scale);
-        return q < kBuckets ? q : kBuckets - 1;
-    };
-    each([&](const uint2& x) { atomicAdd(&b.part[part_of(x.x)], 1u); });
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) b.part[tid + j * G] = 0u;
     __syncthreads();
-    const uint32_t c = b.part[tid];
-    const uint32_t incl = wave_inclusive_scan(c), cmax = __ockl_wfred_max_u32(c);
-    if (lane == 63) {   // (the last readers of red ended before the barrier)
+    const bool even = b.even != 0u;
+    const uint32_t lo = b.lo;
+    const float scale = b.scale;
+    auto part_of = [&](uint64_t x) {   // monotone in x
+        if (even) {
+            const uint32_t d = (uint32_t)(x >> 32);
+            return (uint32_t)fminf((float)(d > lo ? d - lo : 0u) * scale, (float)(kParts - 1));
+        }
+        int k = 0;
+#pragma unroll
+        for (int h = kS / 2; h > 0; h >>= 1) k += b.split[k + h] <= x ? h : 0;
+        const uint64_t from = b.split[k], to = b.split[k + 1];
+        const float f = (float)(x > from ? x - from : 0ull) *
+                        ((float)kSub * __builtin_amdgcn_rcpf((float)(to - from) + 1.f));
+        return (uint32_t)(k * kSub + (int)fminf(f, (float)(kSub - 1)));
+    };
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (tid + e * G < n) {
+            at[e] = part_of(v[e]);
+            atomicAdd(&b.part[at[e]], 1u);
+        }
+    if constexpr (E == 0)
+        for (int i = tid; i < n; i += G) atomicAdd(&b.part[part_of(composite(in[start + i]))], 1u);
+    __syncthreads();
+    uint32_t c[kPer], sum = 0u, cmax = 0u;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        c[j] = b.part[tid * kPer + j];
+        sum += c[j];
+        cmax = max(cmax, c[j]);
+    }
+    const uint32_t incl = wave_inclusive_scan(sum);
+    cmax = __ockl_wfred_max_u32(cmax);
+    if (lane == 63) {
         b.red[wave] = incl;
         b.red[kWaves + wave] = cmax;
     }
     __syncthreads();
-    uint32_t first = incl - c, most = 0u;
+    uint32_t first = incl - sum, largest = 0u;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
         first += w < wave ? b.red[w] : 0u;
-        most = b.red[kWaves + w] > most ? b.red[kWaves + w] : most;
+        largest = b.red[kWaves + w] > largest ? b.red[kWaves + w] : largest;
     }
-    if (most > kPartMax) return false;
-    b.part[tid] = first;
-    if (tid == kBuckets - 1) b.part[kBuckets] = first + c;
+    if (largest > kPartMax) return false;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        b.part[tid * kPer + j] = first;
+        first += c[j];
+    }
     __syncthreads();
-    each([&](const uint2& x) {
-        const int q = part_of(x.x);
-        s[b.part[q] + atomicAdd(&b.fill[q], 1u)] = composite(x);
-    });
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (tid + e * G < n) s[atomicAdd(&b.part[at[e]], 1u)] = v[e];
+    if constexpr (E == 0)
+        for (int i = tid; i < n; i += G) {
+            const uint64_t x = composite(in[start + i]);
+            s[atomicAdd(&b.part[part_of(x)], 1u)] = x;
+        }
     __syncthreads();
-    // the place of the entry in slot i of s: equal entries (the caller's own
-    // lists may repeat a pair) go by their slots, so that no two share a place
-    auto place_of = [&](int i, uint64_t v) {
-        const int q = part_of((uint32_t)(v >> 32));
-        const uint32_t p0 = b.part[q], p1 = b.part[q + 1];
-        uint32_t r = p0;
-        for (uint32_t p = p0; p < p1; ++p) {
+    // by slots, not by this thread's own entries: a wave's lanes then count in the
+    // same few parts, and their places, close to their slots, fill whole lines
+    // (by own entries a wave waits for the largest part any of them is in: 900 runs
+    // of 8,000 entries of a wall and its background 485 us, 235 by slots)
+#pragma unroll 1
+    for (int i = tid; i < n; i += G) {
+        const uint64_t x = s[i];
+        const uint32_t q = part_of(x), p1 = b.part[q];
+        uint32_t r = q > 0u ? b.part[q - 1u] : 0u;
+        for (uint32_t p = r; p < p1; ++p) {
             const uint64_t y = s[p];
-            r += y < v || (y == v && p < (uint32_t)i) ? 1u : 0u;
+            // equal entries (the caller's own lists may repeat a pair) by their
+            // slots, so that no two share a place
+            r += y < x || (y == x && p < (uint32_t)i) ? 1u : 0u;
         }
-        return r;
-    };
-    if constexpr (HELD) {
-        const uint64_t v0 = tid < n ? s[tid] : 0ull, v1 = i1 < n ? s[i1] : 0ull;
-        const uint32_t r0 = tid < n ? place_of(tid, v0) : 0u, r1 = i1 < n ? place_of(i1, v1) : 0u;
-        __syncthreads();
-        if (tid < n) s[r0] = v0;
-        if (i1 < n) s[r1] = v1;
-        __syncthreads();
-        for (int i = tid; i < n; i += kLongThreads) {
-            const uint64_t v = s[i];
-            keys[start + i] = (tile << 32) | (v >> 32);
-            vals[start + i] = (uint32_t)v;
-        }
-    } else {
-        for (int i = tid; i < n; i += kLongThreads) {
-            const uint64_t v = s[i];
-            const uint32_t r = place_of(i, v);
-            keys[start + r] = (tile << 32) | (v >> 32);
-            vals[start + r] = (uint32_t)v;
-        }
+        keys[start + r] = (tile << 32) | (x >> 32);
+        vals[start + r] = (uint32_t)x;
     }
     return true;
 }
@@ -528,7 +548,7 @@ FS_DEV void sort_run_global(uint2* a, uint2* b, uint64_t tile, uint32_t start, u
                             uint64_t* keys, uint32_t* __restrict__ vals, uint32_t* hist, uint32_t* wcnt,
                             uint32_t* flag) {
     constexpr int kWaves = NT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = own_thread(), lane = tid & 63, wave = tid >> 6;
     const uint64_t lt = (1ull << lane) - 1ull;
     uint2* src = a + start;
     uint2* dst = b + start;
@@ -593,34 +613,75 @@ FS_DEV void sort_run_global(uint2* a, uint2* b, uint64_t tile, uint32_t start, u
     }
 }
 
-// Runs longer than kWaveCap, from the list: up to kLargeCap entries in LDS,
-// longer ones by the global radix sort.
+// Runs longer than kWaveCap, from the list: up to kMidCap entries four at a time,
+// by a quarter of the workgroup each (3,600 runs of 300 entries, depths spread and
+// bunched: 52 and 59 us, 73 and 138 by whole workgroups with equal parts, 58 and 58 by
+// a wave each, which for a list as short as the 1M-surfel 1280x720 frame's is 4 us
+// slower), up to kLargeCap by the workgroup, longer ones by the global radix sort.
 // Two workgroups per CU (64 VGPRs at most) keep every long run of a frame
 // in flight at once.
 __global__ void __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(8)))
 sort_long_runs_kernel(uint2* __restrict__ in, const uint32_t* __restrict__ ranges,
                       const uint32_t* __restrict__ long_list, const uint32_t* __restrict__ long_count,
                       uint64_t* keys, uint32_t* __restrict__ vals) {
-    __shared__ uint64_t s[kLargeCap];
-    __shared__ BucketShared parts;
-    const uint32_t count = *long_count;
-    for (uint32_t it = blockIdx.x; it < count; it += gridDim.x) {
-        const uint64_t t = long_list[it];
-        const uint32_t start = ranges[2 * t], end = ranges[2 * t + 1];
-        const uint32_t n = end - start;
-        if (n <= (uint32_t)kLargeCap) {
-            const bool done = n <= 2u * kLongThreads ? sort_run_buckets<true>(s, parts, in, t, start, (int)n, keys, vals)
-                                                     : sort_run_buckets<false>(s, parts, in, t, start, (int)n, keys, vals);
-            if (!done) sort_run_lds<kLongThreads>(s, in, t, start, (int)n, keys, vals);
-        } else {
-            // the run's own slice of the key array is the radix passes' second
-            // buffer; LDS holds their counters
-            uint32_t* hist = reinterpret_cast<uint32_t*>(s);
-            uint32_t* wcnt = hist + 256;
-            uint32_t* flag = wcnt + (kLongThreads / 64) * 256;
-            sort_run_global<kLongThreads>(in, reinterpret_cast<uint2*>(keys), t, start, n, keys, vals, hist, wcnt, flag);
+    constexpr int kMid = 256, kMids = kLongThreads / kMid;   // threads per run of at most kMidCap entries
+    static_assert(kMidCap == 2 * kMid, "two entries per thread");
+    __shared__ union {
+        struct {
+            uint64_t s[kLargeCap];
+            PartShared<kLongThreads, 2048> parts;
+        } all;
+        struct {
+            uint64_t s[kMidCap];
+            PartShared<kMid, 512> parts;
+        } mid[kMids];
+    } sm;
+    uint64_t* s = sm.all.s;
+    __shared__ uint32_t s_todo[kLongThreads];   // this workgroup's runs: short ones from the front, others from the back
+    __shared__ uint32_t s_num[2];
+    const int tid = (int)threadIdx.x;
+    const uint32_t count = *long_count, grid = gridDim.x;
+    for (uint32_t base = blockIdx.x; base < count; base += grid * kLongThreads) {
+        // every grid-th run of the list, looked up in one round trip
+        if (tid < 2) s_num[tid] = 0u;
+        __syncthreads();
+        const uint32_t mine = (count - base + grid - 1) / grid;
+        if ((uint32_t)tid < mine) {
+            const uint32_t t = long_list[base + (uint32_t)tid * grid];
+            const bool mid = ranges[2 * (int64_t)t + 1] - ranges[2 * (int64_t)t] <= (uint32_t)kMidCap;
+            const uint32_t i = atomicAdd(&s_num[mid ? 0 : 1], 1u);
+            s_todo[mid ? i : kLongThreads - 1 - i] = t;
         }
-        __syncthreads();   // LDS is reused by the next run
+        __syncthreads();
+        const uint32_t mids = __builtin_amdgcn_readfirstlane(s_num[0]), longs = __builtin_amdgcn_readfirstlane(s_num[1]);
+        for (uint32_t i = 0; i < mids; i += kMids) {
+            const uint32_t g = __builtin_amdgcn_readfirstlane((uint32_t)tid / kMid);
+            const uint32_t t = __builtin_amdgcn_readfirstlane(i + g < mids ? s_todo[i + g] : 0u);   // (uniform in a wave)
+            const uint32_t start = ranges[2 * (int64_t)t];
+            const uint32_t n = i + g < mids ? ranges[2 * (int64_t)t + 1] - start : 0u;
+            sort_run_parts<kMid, 2>(sm.mid[g].s, sm.mid[g].parts, in, t, start, (int)n, keys, vals);
+            __syncthreads();   // LDS is reused by the next runs
+        }
+        for (uint32_t i = 0; i < longs; ++i) {
+            const uint32_t t = __builtin_amdgcn_readfirstlane(s_todo[kLongThreads - 1 - i]);
+            const uint32_t start = ranges[2 * (int64_t)t], n = ranges[2 * (int64_t)t + 1] - start;
+            const bool done =
+                n <= 1u * kLongThreads   ? sort_run_parts<kLongThreads, 1>(s, sm.all.parts, in, t, start, (int)n, keys, vals)
+                : n <= 2u * kLongThreads ? sort_run_parts<kLongThreads, 2>(s, sm.all.parts, in, t, start, (int)n, keys, vals)
+                : n <= (uint32_t)kLargeCap
+                    ? sort_run_parts<kLongThreads, 0>(s, sm.all.parts, in, t, start, (int)n, keys, vals)
+                    : false;
+            if (!done) {
+                // the run's own slice of the key array is the radix passes' second
+                // buffer; LDS holds their counters
+                uint32_t* hist = reinterpret_cast<uint32_t*>(s);
+                uint32_t* wcnt = hist + 256;
+                uint32_t* flag = wcnt + (kLongThreads / 64) * 256;
+                sort_run_global<kLongThreads>(in, reinterpret_cast<uint2*>(keys), t, start, n, keys, vals, hist, wcnt,
+                                              flag);
+            }
+            __syncthreads();   // LDS is reused by the next run
+        }
     }
 }
 

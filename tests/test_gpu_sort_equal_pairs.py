@@ -1,5 +1,5 @@
 """fs_sort orders the caller's pairs by (key, value), also where a list repeats a
-pair: every copy keeps a place of its own.  Runs at the edges of the run sorts
+pair (1,500 times: more than a part of the distribution takes): every copy keeps a place of its own.  Runs at the edges of the run sorts
 (one wave, a workgroup's distribution, radix), bit-exact against a stable sort."""
 from __future__ import annotations
 
@@ -17,7 +17,7 @@ SIZES = (2, 64, 129, 256, 257, 300, 511, 512, 513, 1024, 1025, 2048, 2049, 4096,
 
 
 @pytest.mark.parametrize("depths", ["spread", "bunched"])
-@pytest.mark.parametrize("copies", [2, 5, 60])
+@pytest.mark.parametrize("copies", [2, 5, 60, 1500])
 def test_repeated_pairs(depths, copies):
     print(f"[case] repeated pairs {depths} x{copies}", flush=True)
     rng = np.random.default_rng(copies)
