@@ -33,6 +33,12 @@ namespace {
 constexpr int kSelBatch = 32;   // list entries staged per step in the selection pass
 constexpr int kEvalPairs = 2;   // (entry, pixel) pairs a selection lane evaluates per round
 constexpr uint32_t kSelLong = 48;   // blocks with longer tile lists are selected first
+constexpr uint32_t kSelCoop = 256;      // by weight: blocks with longer lists take a workgroup each (1M surfels,
+                                        // 1280x720: render 351 us, 365 from 192, 388 from 128),
+constexpr uint32_t kCoopMost = 2560;    // unless there are more of them than that (2,400 such blocks: 472 us,
+                                        // 535 without; 3,480: 522 with, 472 without),
+constexpr uint32_t kCoopAll = 1024;     // and all long-list blocks if there are no more than that (917 of them:
+                                        // 84 us, 95 without; 1,950: 111 with, 107 without)
 constexpr int kSelGroup = 256;       // blocks per group of the long-block list
 constexpr int kGatherThreads = 256;
 constexpr int kGatherUnroll = 8;  // (surfel, weight) pairs whose row loads are in flight together
@@ -58,21 +64,23 @@ struct SelShared {
 };
 
 // The blocks whose tile list holds more than kSelLong entries, per group of
-// kSelGroup consecutive blocks: their indices at long[g * kSelGroup ..] and
-// their number at counts[g].  No atomics and nothing to clear beforehand.
+// kSelGroup consecutive blocks: their indices at long[g * kSelGroup ..], those
+// with more than `most` entries first, and counts[g] = the number of those | the
+// number of the others << 16.  No atomics and nothing to clear beforehand.
 __global__ void __launch_bounds__(kSelGroup)
-select_long_kernel(const uint32_t* __restrict__ ranges, int sb2, int64_t nblocks, uint32_t* __restrict__ lng,
-                   uint32_t* __restrict__ counts) {
+select_long_kernel(const uint32_t* __restrict__ ranges, int sb2, int64_t nblocks, uint32_t most,
+                   uint32_t* __restrict__ lng, uint32_t* __restrict__ counts) {
     __shared__ uint32_t s_wave[kSelGroup / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t b = (int64_t)blockIdx.x * kSelGroup + tid;
-    bool is_long = false;
+    uint32_t len = 0u;
     if (b < nblocks) {
         const int64_t t = b / sb2;
-        is_long = ranges[2 * t + 1] - ranges[2 * t] > kSelLong;
+        len = ranges[2 * t + 1] - ranges[2 * t];
     }
-    const uint64_t m = __ballot(is_long);
-    if (lane == 0) s_wave[wave] = (uint32_t)__popcll(m);
+    const bool longest = len > kSelLong && len > most, is_long = len > kSelLong && !longest;
+    const uint64_t m1 = __ballot(longest), m2 = __ballot(is_long);
+    if (lane == 0) s_wave[wave] = (uint32_t)__popcll(m1) | (uint32_t)__popcll(m2) << 16;
     __syncthreads();
     uint32_t before = 0, total = 0;
 #pragma unroll
@@ -80,7 +88,10 @@ select_long_kernel(const uint32_t* __restrict__ ranges, int sb2, int64_t nblocks
         before += w < wave ? s_wave[w] : 0u;
         total += s_wave[w];
     }
-    if (is_long) lng[(int64_t)blockIdx.x * kSelGroup + before + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)b;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    uint32_t* __restrict__ list = lng + (int64_t)blockIdx.x * kSelGroup;
+    if (longest) list[(before & 0xffffu) + __popcll(m1 & lt)] = (uint32_t)b;
+    if (is_long) list[(total & 0xffffu) + (before >> 16) + __popcll(m2 & lt)] = (uint32_t)b;
     if (tid == 0) counts[blockIdx.x] = total;
 }
 
@@ -99,14 +110,16 @@ FS_DEV void sel_sync() {
 }
 
 // Block of a selection wave.  The first nlong workgroups (dispatched first; 0:
-// no such part) take the long-list blocks: the i-th wave the i-th of them, or
-// with COOP one per workgroup, all its waves together.  The other workgroups
-// take every block in grid order, one per wave, and skip the long ones.  Returns
-// -1 for a wave without a block.
-template <int WPG, bool COOP>
+// no such part) take the long-list blocks, the i-th wave the i-th of them.  By
+// weight, the longest ones (more than kSelCoop entries) come before the others and
+// take a workgroup each, all its waves together (coop), as long as there are at
+// most kCoopMost of them; all of them do if they are at most kCoopAll.  The other workgroups take every block in grid order, one
+// per wave, and skip the long ones.  Returns -1 for a wave without a block.
+template <int WPG, bool BYW>
 FS_DEV int64_t select_block_of(int64_t nblocks, uint32_t nlong, const fs_camera* cams, int S, int sb2,
-                               const uint32_t* ranges, const uint32_t* lng, const uint32_t* counts) {
+                               const uint32_t* ranges, const uint32_t* lng, const uint32_t* counts, bool& coop) {
     const uint32_t wave = threadIdx.x >> 6, wg = blockIdx.x;
+    coop = false;
     if (wg >= nlong) {
         const int64_t nwg = (nblocks + WPG - 1) / WPG;
         const int64_t chunk = block_row_chunk(cams, S) / WPG;
@@ -115,21 +128,42 @@ FS_DEV int64_t select_block_of(int64_t nblocks, uint32_t nlong, const fs_camera*
         const int64_t t = b / sb2;
         return nlong != 0u && ranges[2 * t + 1] - ranges[2 * t] > kSelLong ? -1 : b;
     }
-    const uint32_t i = COOP ? wg : wg * WPG + wave;   // the long block of this wave
+    const uint32_t groups = (uint32_t)((nblocks + kSelGroup - 1) / kSelGroup);
+    const int lane = threadIdx.x & 63;
+    uint32_t i = wg * WPG + wave;      // the long block of this wave,
+    uint32_t first = ~0u, rest = ~0u;  // counted over the longest ones, the others or (both masks) all
+    if constexpr (BYW && WPG > 1) {
+        uint32_t longest = 0u, all = 0u;
+        for (uint32_t c0 = 0; c0 < groups; c0 += 64) {
+            const uint32_t c = c0 + lane < groups ? counts[c0 + lane] : 0u;
+            longest += __ockl_wfred_add_u32(c & 0xffffu);
+            all += __ockl_wfred_add_u32((c & 0xffffu) + (c >> 16));
+        }
+        if (all <= kCoopAll) {
+            coop = wg < all;
+            i = wg;
+        } else if (longest <= kCoopMost) {
+            coop = wg < longest;
+            i = coop ? wg : (wg - longest) * WPG + wave;
+            first = coop ? ~0u : 0u;
+            rest = ~first;
+        }
+    }
     // the group holding it: running sum of the groups' counts (taking the i /
     // groups-th block of group i mod groups needs no sum but starts some long
     // blocks later: 158 -> 163 us on the 300k-surfel 640x480 frame)
-    const uint32_t groups = (uint32_t)((nblocks + kSelGroup - 1) / kSelGroup);
-    const int lane = threadIdx.x & 63;
     uint32_t run = 0;
     for (uint32_t c0 = 0; c0 < groups; c0 += 64) {
-        const uint32_t c = c0 + lane < groups ? counts[c0 + lane] : 0u;
+        const uint32_t both = c0 + lane < groups ? counts[c0 + lane] : 0u;
+        // (first K: the longest ones are not told apart)
+        const uint32_t c = BYW ? ((both & 0xffffu) & first) + ((both >> 16) & rest) : both >> 16;
         const uint32_t incl = __ockl_wfscan_add_u32(c, true);
         const uint64_t past = __ballot(run + incl > i);
         if (past) {
             const int l = __builtin_ctzll(past);
             const uint32_t excl = run + __builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(c, l);
-            return lng[(c0 + l) * kSelGroup + (i - excl)];
+            const uint32_t skip = !BYW ? 0u : (uint32_t)__builtin_amdgcn_readlane(both, l) & 0xffffu & ~first;
+            return lng[(c0 + l) * kSelGroup + skip + (i - excl)];
         }
         run += __builtin_amdgcn_readlane(incl, 63);
     }
@@ -176,12 +210,14 @@ struct Heaviest {
         wmin = -1.f;
         imin = 0;
     }
-    FS_DEV void replace(uint32_t p, float x) {   // the lightest by (p, x)
+    FS_DEV void put(int at, uint32_t p, float x) {
 #pragma unroll
         for (int j = 0; j < KC; ++j) {
-            w[j] = j == imin ? x : w[j];
-            pos[j] = j == imin ? p : pos[j];
+            w[j] = j == at ? x : w[j];
+            pos[j] = j == at ? p : pos[j];
         }
+    }
+    FS_DEV void lightest() {   // of a full list
         wmin = w[0];
         imin = 0;
         uint32_t pm = pos[0];
@@ -225,8 +261,10 @@ struct Heaviest {
 // order as in the first-K mode, and every pair's position becomes its slot.
 // EXT (first K only): the low-pass response (o.lowpass) and the depth and
 // normal outputs, summed with the weights the lists hold.
+// Four waves per SIMD for the forms that pass 128 registers a little (by weight and K <= 8,
+// 130 registers let three: render of 1M surfels, 1280x720, 433 us, 380 with four).
 template <int KC, bool BYW, bool EXT, int WPG>
-__global__ void __launch_bounds__(64 * WPG)
+__global__ void __launch_bounds__(64 * WPG) __attribute__((amdgpu_waves_per_eu(KC == 8 && (BYW || EXT) ? 4 : 1)))
 topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restrict__ keys,
                    const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, uint32_t n,
                    int64_t num_records, const fs_camera* __restrict__ cams, int num_views, int S, fs_opts o,
@@ -242,18 +280,21 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
     static_assert(!BYW || KC > 0, "the by-weight lists live in LDS");
     static_assert(!(BYW && EXT), "no extended outputs for the by-weight selection");
     __shared__ SelShared<KC, BYW, EXT> sm_waves[WPG];
-    // coop (by weight): a long-list block with the whole workgroup, whose first
+    // coop (by weight): one of the longest lists with the whole workgroup, whose first
     // wave does everything but the pair evaluations, which all waves share: they
     // are half of a batch's time, and the kernel lasts as long as its longest
-    // walks, which only T_stop ends (300k surfels, 640x480, K = 8: frame 259 ->
-    // 235 us; the first-K walks are short enough that the halved number of
-    // blocks in work costs more: 303 -> 315 us on the 1M-surfel 1280x720 frame)
-    const bool coop = BYW && WPG > 1 && blockIdx.x < nlong;   // uniform over the workgroup
+    // walks, which only T_stop ends (render of the
+    // 1M-surfel 640x480 frame, K = 8: 226 us, 282 with a wave each; of 100k surfels
+    // 79 and 92; with more such blocks than workgroups in flight they only hold
+    // up the others: 1M surfels, 1280x720, tile 16: 472, 532 with all of them; the
+    // first-K walks are short enough that the halved number of blocks in work costs
+    // more: 303 -> 315 us on the 1M-surfel 1280x720 frame)
+    bool coop;   // uniform over the workgroup
+    const int sb2 = (S / 8) * (S / 8);
+    const int64_t block = select_block_of<WPG, BYW>(nblocks, nlong, cams, S, sb2, ranges, lng, lcounts, coop);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     SelShared<KC, BYW, EXT>& sm = sm_waves[coop ? 0 : wave];
     const int lane = threadIdx.x & 63;
-    const int sb2 = (S / 8) * (S / 8);
-    const int64_t block = select_block_of<WPG, BYW>(nblocks, nlong, cams, S, sb2, ranges, lng, lcounts);
     if (block < 0) return;   // uniform across the wave, and across the workgroup if coop
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
     if (!bp.valid) return;
@@ -442,11 +483,9 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
         if (coop) {
             if (lane == 0) sm.total = total;
             __syncthreads();   // the batch's records, pair counts and masks are in place
-            evaluate(total, 0, WPG * 64 * kEvalPairs);
-            __syncthreads();   // every wave's accepted pairs are in the masks
-        } else {
-            evaluate(total, 0, 64 * kEvalPairs);
         }
+        evaluate(total, 0, (coop ? WPG : 1) * 64 * kEvalPairs);
+        if (coop) __syncthreads();   // every wave's accepted pairs are in the masks
         sel_sync<WPG>();
         // (b) lane = pixel: front-to-back transmittance over its accepted
         //     entries (alpha recomputed from the same response: the accepted
@@ -483,8 +522,9 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
                 // than any entry); a new entry enters only if strictly heavier
                 const float w = (float)((double)al * T);
                 if (w > best.wmin) {
-                    best.replace(b0 + (uint32_t)e, w);
+                    best.put(cnt < K ? cnt : best.imin, b0 + (uint32_t)e, w);
                     cnt += cnt < K ? 1 : 0;
+                    if (cnt == K) best.lightest();
                 }
                 T = Tn;
                 last = (int)(b0 + e);
@@ -550,7 +590,9 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
         __syncthreads();
     }
 
-    if constexpr (BYW) {
+    // (a block that lists nothing has no rows to number: half of the 20k-surfel
+    // 1280x720 frame's blocks, render 103 -> 88 us)
+    if constexpr (BYW) if (__any(cnt > 0)) {
         constexpr int LOGE = KC == 8 ? 3 : 4;
         static_assert(KC == (1 << LOGE), "one register per list slot");
         uint2* __restrict__ lst = &sm.list[lane * KC];
@@ -1078,7 +1120,9 @@ hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, 
         return hipErrorInvalidValue;
     // (a launch holds fewer than 2^32 threads: without the long part beyond that)
     const int64_t long_waves = (nblocks + kSelGroup - 1) / kSelGroup * kSelGroup;
-    const int64_t long_wgs = o.topk_mode == FS_TOPK_WEIGHT ? long_waves : long_waves / 2;
+    int64_t long_wgs = long_waves / 2;
+    if (o.topk_mode == FS_TOPK_WEIGHT)   // and up to kCoopMost more for blocks that take a workgroup each
+        long_wgs = long_waves < kCoopMost ? long_waves : long_waves / 2 + kCoopMost / 2;
     uint32_t nlong = (long_wgs + nblocks / 2 + 1) * 128 < (int64_t(1) << 32) ? (uint32_t)long_wgs : 0u;
     // first-K frames whose blocks are all in flight at once (sixteen waves on each
     // of 256 CUs) need no order: without the list launch and the waves that find
@@ -1087,7 +1131,8 @@ hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, 
     if (o.topk_mode != FS_TOPK_WEIGHT && nblocks <= 4096) nlong = 0u;
     if (nlong != 0u)
         hipLaunchKernelGGL(select_long_kernel, dim3((unsigned)((nblocks + kSelGroup - 1) / kSelGroup)), dim3(kSelGroup),
-                           0, s, ranges, sb * sb, nblocks, ws.sel_long, ws.sel_counts);
+                           0, s, ranges, sb * sb, nblocks, o.topk_mode == FS_TOPK_WEIGHT ? kSelCoop : ~0u, ws.sel_long,
+                           ws.sel_counts);
 #define FS_SEL_LAUNCH(WPG)                                                                                      \
     hipLaunchKernelGGL(FS_SEL_KERN(WPG), dim3((unsigned)(nlong + (nblocks + WPG - 1) / WPG)), dim3(64 * WPG), 0, s,   \
                        records, keys, vals, ranges, (uint32_t)n, n * num_views, cams, num_views, o.tile, o, nblocks,  \
