@@ -494,6 +494,16 @@ FS_DEV void render_block_wide(int64_t block, WideShared<NVT, FT, NW, BG, EXT, FI
     float* __restrict__ image = reinterpret_cast<float*>(&sm.feat[0][0]);
     // rows of whole aligned float4 (c0 and clen are multiples of four when C is)
     const bool vec4 = (C & 3) == 0 && (reinterpret_cast<uintptr_t>(out_feat) & 15u) == 0u;
+    if (pbuf < 0 && vec4 && clen == C) {
+        // nothing blended: a pixel row's channels are contiguous
+        const int w = cam.width - bp.x0 < 8 ? cam.width - bp.x0 : 8, h = cam.height - bp.y0 < 8 ? cam.height - bp.y0 : 8;
+        for (int y = wave; y < h; y += NW) {
+            float* __restrict__ row = out_feat + (cam.pixel_offset + (int64_t)(bp.y0 + y) * cam.width + bp.x0) * C;
+            for (int t = lane; t < w * C >> 2; t += 64)
+                __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(row) + t);
+        }
+        return;
+    }
     const int per = vec4 ? clen >> 2 : clen;
     const uint32_t inv = ((1u << 20) + (uint32_t)per - 1u) / (uint32_t)per;   // exact division of t < 64 * 128 by per
 #pragma unroll 1
@@ -526,8 +536,11 @@ FS_DEV void render_block_wide(int64_t block, WideShared<NVT, FT, NW, BG, EXT, FI
     }
 }
 
+// Four waves per SIMD for up to four vectors per lane (64 channels, 128 bfloat16):
+// a few registers over 128 let three (300k surfels, 1280x720, C = 64, tile 16: render
+// 193 -> 163 us; with depth and normals, 200k, 640x480, C = 16: 88 -> 76).
 template <int NVT, typename FT, int NW, int BG, bool VEC, bool EXT, bool FILTER>
-__global__ void __launch_bounds__(NW * 64)
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NVT <= 4 ? 4 : 1)))
 render_wide_kernel(const FsRecord* __restrict__ records, const uint64_t* __restrict__ keys,
                    const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, const FT* __restrict__ feats,
                    int C, int64_t n, int64_t num_records, const fs_camera* __restrict__ cams, int num_views, int S,
@@ -774,7 +787,10 @@ hipError_t launch_wide(const FsRecord* records, const uint64_t* keys, const uint
             per_cu = 1;
         grid = (int64_t)device_cus() * per_cu;
     }
-    if (grid > 0 && blocks > grid) {
+    // and with enough lists to order: with fewer surfels than blocks most blocks
+    // have none (2,000 surfels, 1280x720, C = 64, tile 16: render 61 us with the
+    // queue, 49 without)
+    if (grid > 0 && blocks > grid && n * num_views >= blocks) {
         const uint32_t nb = (uint32_t)blocks;
         const hipError_t e = fs_launch_block_order(ranges, sb * sb, nb, ws, s);
         if (e != hipSuccess) return e;
