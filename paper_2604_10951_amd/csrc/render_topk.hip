@@ -39,6 +39,7 @@ constexpr uint32_t kCoopMost = 2560;    // unless there are more of them than th
                                         // 535 without; 3,480: 522 with, 472 without),
 constexpr uint32_t kCoopAll = 1024;     // and all long-list blocks if there are no more than that (917 of them:
                                         // 84 us, 95 without; 1,950: 111 with, 107 without)
+constexpr int kZeroMax = 256;        // channels up to which the selection writes the zeros of blocks without rows
 constexpr int kSelGroup = 256;       // blocks per group of the long-block list
 constexpr int kGatherThreads = 256;
 constexpr int kGatherUnroll = 8;  // (surfel, weight) pairs whose row loads are in flight together
@@ -674,8 +675,10 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
     // a block that blends nothing gets its zero features here and the gather
     // skips it: the walks leave the memory idle, and two thirds of the
     // 1M-surfel 1280x720 C = 128 image are such blocks (select + gather
-    // 60 + 127 us without, 86 + 80 us with; frame 375 -> 355 us)
-    if (out_feat != nullptr && nslots == 0u) zero_block(out_feat, C, cam, bp);
+    // 60 + 127 us without, 86 + 80 us with; frame 375 -> 355 us).  Wider images hold
+    // a selection wave up for too long: 50k surfels, 640x480, C = 256 96 -> 86 us, but
+    // C = 320 170 -> 179 and C = 1024 282 -> 321
+    if (out_feat != nullptr && C <= kZeroMax && nslots == 0u) zero_block(out_feat, C, cam, bp);
     if (inside) {
         if (out_T) out_T[pix] = (float)T;
         out_n[pix] = cnt;
@@ -820,7 +823,7 @@ topk_gather_general_kernel(const uint2* __restrict__ pairs, const int32_t* __res
     const int64_t block = g / kGroups;
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
     if (!bp.valid) return;   // uniform over the workgroup
-    if (!LABEL && nrows[block] == 0u) return;   // the selection wrote its zeros
+    if (!LABEL && C <= kZeroMax && nrows[block] == 0u) return;   // the selection wrote its zeros
     const fs_camera& cam = cams[bp.view];
     const bool compact = K <= kCompactK;   // the selection's list layout
     if (compact) {
@@ -924,7 +927,7 @@ topk_gather_lds_kernel(const uint2* __restrict__ pairs, const int32_t* __restric
     for (int v = 0; v < NVT; ++v) has_vec[v] = q + v * TPP < nv;
     const uint32_t nr = nrows[block];
     const uint32_t R = nr & 0xffffu, NP = nr >> 16;   // rows and listed pairs of the block
-    if (!LABEL && R == 0u) return;                    // the selection wrote its zeros
+    if (!LABEL && C <= kZeroMax && R == 0u) return;   // the selection wrote its zeros
     const uint32_t* __restrict__ rowlist = rows + block * 64 * (int64_t)K;
     // lists, counts and the row list: one round trip
     if (R > 0)
