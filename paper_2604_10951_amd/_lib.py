@@ -21,6 +21,7 @@ FS_TOPK_FIRST, FS_TOPK_WEIGHT = 0, 1
 FS_RECORD_BYTES = 96
 FS_TILE_CACHE_WORDS = 4
 FS_GRAD_RECORD_FLOATS = 12
+HIP_MEMCPY_DEVICE_TO_HOST = 2
 
 
 class FsCamera(ctypes.Structure):
@@ -94,6 +95,9 @@ def load(path: str = LIB_PATH):
         fn = getattr(lib, name)
         fn.argtypes = argtypes
         fn.restype = restype
+    # of the HIP runtime the library is linked with
+    lib.hipMemcpyAsync.argtypes = [P, P, ctypes.c_size_t, ctypes.c_int, P]
+    lib.hipMemcpyAsync.restype = ctypes.c_int
     _lib = lib
     return lib
 
@@ -101,6 +105,11 @@ def load(path: str = LIB_PATH):
 def check(status: int, what: str) -> None:
     if status != FS_OK:
         raise FastSegSimError(status, what)
+
+
+def check_hip(error: int, what: str) -> None:
+    if error != 0:
+        raise FastSegSimError(FS_ERR_HIP, f"{what} (HIP error {error})")
 
 
 def make_opts(tile: int = 16, topk: int = 0, tile_mode: int = FS_TILES_PRECISE, feat_dtype: int = FS_FEAT_F32,

@@ -88,6 +88,7 @@ class Rasterizer:
         self.cams_dev = torch.frombuffer(bytearray(raw), dtype=torch.uint8).to(self.device)
         self.capacity = int(pair_capacity)
         self._n = -1
+        self._pairs = -1      # pairs of the last frame rendered from these buffers (-1: not known)
         self._bufs: dict[str, torch.Tensor] = {}
         # records, pairs and ranges are shared by every frame this object
         # renders; each preprocess refills them and bumps the generation, so a
@@ -120,6 +121,7 @@ class Rasterizer:
             self._bufs["num_pairs"] = torch.zeros(1, dtype=torch.int64, device=self.device)
             self._bufs["ranges"] = torch.empty(self.total_tiles * 2, dtype=torch.int32, device=self.device)
             self._n = n
+            self._pairs = -1
         if capacity > self.capacity or "keys" not in self._bufs:
             self.capacity = max(capacity, self.capacity, 1024)
             self._bufs["keys"] = torch.empty(self.capacity, dtype=torch.int64, device=self.device)
@@ -218,32 +220,50 @@ class Rasterizer:
         _f32(quats, (n, 4), "quats")
         _f32(opacity, (n,), "opacity")
         self.preprocess(means, scales, quats, opacity)
-        # The whole frame is enqueued before the host waits for the pair count,
-        # which is copied back as soon as the bin stage has it: waiting first
-        # left the GPU idle for the readback and the launches behind it
-        # (2,000 surfels, 128x128: 132 -> 92 us a frame).
-        self._bin_nosync(means, scales, quats, opacity)
-        if "pairs_host" not in self._bufs:
-            self._bufs["pairs_host"] = torch.empty(1, dtype=torch.int64, pin_memory=True)
-        b = self._bufs
-        counted = torch.cuda.Event()
-        with torch.cuda.device(self.device):
-            b["pairs_host"].copy_(b["num_pairs"], non_blocking=True)
-            counted.record(torch.cuda.current_stream(self.device))
-        self.sort(-1)
-        out = self.render_forward(feats, want_last=want_last, want_idx=want_idx, want_depth=want_depth,
-                                  want_normal=want_normal)
-        counted.synchronize()
-        P = int(b["pairs_host"][0])
-        if P > self.capacity:   # too few pair slots: grow them and take the frame from its bin stage again
-            torch.cuda.current_stream(self.device).synchronize()   # the enqueued stages still read the old buffers
-            self._ensure(n, int(P * 1.25) + 1024)
+        want = dict(want_last=want_last, want_idx=want_idx, want_depth=want_depth, want_normal=want_normal)
+        if self._pairs < 0 or 8 * self._pairs > 7 * self.capacity:
+            # the first frame of these buffers, or one that may outgrow them: the
+            # pair count is waited for before anything is sorted
             P = self.bin(means, scales, quats, opacity)
             self.sort(P)
-            self.render_forward(feats, out=out)
+            out = self.render_forward(feats, **want)
+            if "pairs_host" not in self._bufs:   # for the frames that follow, made while the GPU renders
+                self._bufs["pairs_host"] = torch.empty(1, dtype=torch.int64, pin_memory=True)
+                self._counted = torch.cuda.Event()
+        else:
+            P, out = self._render_ahead(means, scales, quats, opacity, feats, want)
+        self._pairs = P
+        b = self._bufs
         return Frame(out["feat"], out["T"], out["n"], out["last"], out["idx"], P, b["records"], b["tiles"],
                      b["keys"], b["vals"], b["ranges"].view(self.total_tiles, 2), self.generation, out.get("depth"),
                      out.get("normal"))
+
+    def _render_ahead(self, means, scales, quats, opacity, feats, want: dict):
+        """The stages after preprocess, all enqueued before the host waits for
+        the pair count, which is copied back as soon as the bin stage has it:
+        waiting first leaves the GPU idle for the readback and the launches
+        behind it (2,000 surfels, 128x128: frame after frame 138 -> 78 us, a frame
+        on new inputs that is waited for 148 -> 129; with an event of its own and
+        a torch copy in every frame 86 and 164)."""
+        b = self._bufs
+        stream = torch.cuda.current_stream(self.device)
+        self._bin_nosync(means, scales, quats, opacity)
+        L.check_hip(self.lib.hipMemcpyAsync(_p(b["pairs_host"]), _p(b["num_pairs"]), 8, L.HIP_MEMCPY_DEVICE_TO_HOST,
+                                            ctypes.c_void_p(stream.cuda_stream)), "pair count readback")
+        self._counted.record(stream)
+        try:
+            self.sort(-1)
+            out = self.render_forward(feats, **want)
+        finally:
+            self._counted.synchronize()
+        P = ctypes.c_int64.from_address(b["pairs_host"].data_ptr()).value
+        if P > self.capacity:   # too few pair slots: grow them and take the frame from its bin stage again
+            stream.synchronize()   # the enqueued stages still read the old buffers
+            self._ensure(means.shape[0], int(P * 1.25) + 1024)
+            P = self.bin(means, scales, quats, opacity)
+            self.sort(P)
+            self.render_forward(feats, out=out)
+        return P, out
 
     def render_nosync(self, means, scales, quats, opacity, feats, out: dict, counters=None, events=None) -> None:
         """All four stages without any host synchronisation (the pair count
