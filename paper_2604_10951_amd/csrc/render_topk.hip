@@ -39,7 +39,7 @@ constexpr uint32_t kCoopMost = 2560;    // unless there are more of them than th
                                         // 535 without; 3,480: 522 with, 472 without),
 constexpr uint32_t kCoopAll = 1024;     // and all long-list blocks if there are no more than that (917 of them:
                                         // 84 us, 95 without; 1,950: 111 with, 107 without)
-constexpr int kZeroMax = 256;        // channels up to which the selection writes the zeros of blocks without rows
+constexpr int kZeroVectors = 64;    // widest rows (float32; bfloat16: 32) of blocks whose zeros the selection writes
 constexpr int kSelGroup = 256;       // blocks per group of the long-block list
 constexpr int kGatherThreads = 256;
 constexpr int kGatherUnroll = 8;  // (surfel, weight) pairs whose row loads are in flight together
@@ -66,8 +66,8 @@ struct SelShared {
 
 // The blocks whose tile list holds more than kSelLong entries, per group of
 // kSelGroup consecutive blocks: their indices at long[g * kSelGroup ..], those
-// with more than `most` entries first, and counts[g] = the number of those | the
-// number of the others << 16.  No atomics and nothing to clear beforehand.
+// with more than `most` entries first, and counts[g] = the number of those << 16 |
+// the number of the others.  No atomics and nothing to clear beforehand.
 __global__ void __launch_bounds__(kSelGroup)
 select_long_kernel(const uint32_t* __restrict__ ranges, int sb2, int64_t nblocks, uint32_t most,
                    uint32_t* __restrict__ lng, uint32_t* __restrict__ counts) {
@@ -81,7 +81,7 @@ select_long_kernel(const uint32_t* __restrict__ ranges, int sb2, int64_t nblocks
     }
     const bool longest = len > kSelLong && len > most, is_long = len > kSelLong && !longest;
     const uint64_t m1 = __ballot(longest), m2 = __ballot(is_long);
-    if (lane == 0) s_wave[wave] = (uint32_t)__popcll(m1) | (uint32_t)__popcll(m2) << 16;
+    if (lane == 0) s_wave[wave] = (uint32_t)__popcll(m1) << 16 | (uint32_t)__popcll(m2);
     __syncthreads();
     uint32_t before = 0, total = 0;
 #pragma unroll
@@ -91,8 +91,8 @@ select_long_kernel(const uint32_t* __restrict__ ranges, int sb2, int64_t nblocks
     }
     const uint64_t lt = (1ull << lane) - 1ull;
     uint32_t* __restrict__ list = lng + (int64_t)blockIdx.x * kSelGroup;
-    if (longest) list[(before & 0xffffu) + __popcll(m1 & lt)] = (uint32_t)b;
-    if (is_long) list[(total & 0xffffu) + (before >> 16) + __popcll(m2 & lt)] = (uint32_t)b;
+    if (longest) list[(before >> 16) + __popcll(m1 & lt)] = (uint32_t)b;
+    if (is_long) list[(total >> 16) + (before & 0xffffu) + __popcll(m2 & lt)] = (uint32_t)b;
     if (tid == 0) counts[blockIdx.x] = total;
 }
 
@@ -137,7 +137,7 @@ FS_DEV int64_t select_block_of(int64_t nblocks, uint32_t nlong, const fs_camera*
         uint32_t longest = 0u, all = 0u;
         for (uint32_t c0 = 0; c0 < groups; c0 += 64) {
             const uint32_t c = c0 + lane < groups ? counts[c0 + lane] : 0u;
-            longest += __ockl_wfred_add_u32(c & 0xffffu);
+            longest += __ockl_wfred_add_u32(c >> 16);
             all += __ockl_wfred_add_u32((c & 0xffffu) + (c >> 16));
         }
         if (all <= kCoopAll) {
@@ -157,13 +157,13 @@ FS_DEV int64_t select_block_of(int64_t nblocks, uint32_t nlong, const fs_camera*
     for (uint32_t c0 = 0; c0 < groups; c0 += 64) {
         const uint32_t both = c0 + lane < groups ? counts[c0 + lane] : 0u;
         // (first K: the longest ones are not told apart)
-        const uint32_t c = BYW ? ((both & 0xffffu) & first) + ((both >> 16) & rest) : both >> 16;
+        const uint32_t c = BYW ? ((both >> 16) & first) + ((both & 0xffffu) & rest) : both;
         const uint32_t incl = __ockl_wfscan_add_u32(c, true);
         const uint64_t past = __ballot(run + incl > i);
         if (past) {
             const int l = __builtin_ctzll(past);
             const uint32_t excl = run + __builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(c, l);
-            const uint32_t skip = !BYW ? 0u : (uint32_t)__builtin_amdgcn_readlane(both, l) & 0xffffu & ~first;
+            const uint32_t skip = !BYW ? 0u : ((uint32_t)__builtin_amdgcn_readlane(both, l) >> 16) & ~first;
             return lng[(c0 + l) * kSelGroup + skip + (i - excl)];
         }
         run += __builtin_amdgcn_readlane(incl, 63);
@@ -675,10 +675,11 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
     // a block that blends nothing gets its zero features here and the gather
     // skips it: the walks leave the memory idle, and two thirds of the
     // 1M-surfel 1280x720 C = 128 image are such blocks (select + gather
-    // 60 + 127 us without, 86 + 80 us with; frame 375 -> 355 us).  Wider images hold
+    // 60 + 127 us without, 86 + 80 us with; frame 375 -> 355 us.  Wider images hold
     // a selection wave up for too long: 50k surfels, 640x480, C = 256 96 -> 86 us, but
-    // C = 320 170 -> 179 and C = 1024 282 -> 321
-    if (out_feat != nullptr && C <= kZeroMax && nslots == 0u) zero_block(out_feat, C, cam, bp);
+    // C = 320 170 -> 179 and C = 1024 282 -> 321; 200k, 1280x720, bfloat16 C = 256
+    // 323 -> 313, but C = 512 556 -> 570)
+    if (out_feat != nullptr && nslots == 0u) zero_block(out_feat, C, cam, bp);
     if (inside) {
         if (out_T) out_T[pix] = (float)T;
         out_n[pix] = cnt;
@@ -823,7 +824,6 @@ topk_gather_general_kernel(const uint2* __restrict__ pairs, const int32_t* __res
     const int64_t block = g / kGroups;
     const BlockPos bp = locate_block(block, S, 8, cams, num_views);
     if (!bp.valid) return;   // uniform over the workgroup
-    if (!LABEL && C <= kZeroMax && nrows[block] == 0u) return;   // the selection wrote its zeros
     const fs_camera& cam = cams[bp.view];
     const bool compact = K <= kCompactK;   // the selection's list layout
     if (compact) {
@@ -927,7 +927,7 @@ topk_gather_lds_kernel(const uint2* __restrict__ pairs, const int32_t* __restric
     for (int v = 0; v < NVT; ++v) has_vec[v] = q + v * TPP < nv;
     const uint32_t nr = nrows[block];
     const uint32_t R = nr & 0xffffu, NP = nr >> 16;   // rows and listed pairs of the block
-    if (!LABEL && C <= kZeroMax && R == 0u) return;   // the selection wrote its zeros
+    if (!LABEL && 4 * TPP * NVT <= kZeroVectors * (int)sizeof(FT) && R == 0u) return;   // the selection wrote its zeros
     const uint32_t* __restrict__ rowlist = rows + block * 64 * (int64_t)K;
     // lists, counts and the row list: one round trip
     if (R > 0)
@@ -1032,6 +1032,11 @@ topk_gather_lds_kernel(const uint2* __restrict__ pairs, const int32_t* __restric
     }
 }
 
+// Whether the staged gather takes a render, and whether the selection writes the
+// zero features of its blocks without rows (the general gather writes its own).
+bool staged_gather(int ve, int C, int K) { return C % ve == 0 && C / ve <= 64 && K <= kStagedK; }
+bool selection_zeros(int ve, int C, int K) { return staged_gather(ve, C, K) && (ve == 4 || C / ve <= 32); }
+
 template <typename FT, int VE, bool LABEL>
 hipError_t launch_gather(const uint2* pairs, const int32_t* counts, const uint32_t* rows, const uint32_t* nrows,
                          const void* feats, int C, int K, const fs_camera* cams, int num_views, int S,
@@ -1040,7 +1045,7 @@ hipError_t launch_gather(const uint2* pairs, const int32_t* counts, const uint32
     const FT* f = static_cast<const FT*>(feats);
     int tpp = 4;
     while (tpp < nv && tpp < 64) tpp <<= 1;
-    if (VE > 1 && nv <= 64 && K <= kStagedK) {
+    if (VE > 1 && staged_gather(VE, C, K)) {
         if (nblocks >= (int64_t(1) << 32)) return hipErrorInvalidValue;
         // Threads per pixel: 8 when the feature image is written (one store
         // instruction then fills whole 128-B lines), 4 for labels; each
@@ -1164,11 +1169,11 @@ hipError_t fs_launch_render_topk_split(const FsRecord* records, const uint64_t* 
         ws.topk_pair_slots < nblocks * 64 * (int64_t)o.topk || nblocks >= (int64_t(1) << 31) ||
         (out_feat == nullptr) == (out_label == nullptr))
         return hipErrorInvalidValue;
-    hipError_t e = fs_launch_topk_select(records, keys, vals, ranges, n, cams, num_views, total_tiles, o, out_T,
-                                         out_n, out_last, out_idx, out_depth, out_normal, counters, out_feat, C, ws,
-                                         s);
-    if (e != hipSuccess) return e;
     const bool bf16 = o.feat_dtype == FS_FEAT_BF16;
+    hipError_t e = fs_launch_topk_select(records, keys, vals, ranges, n, cams, num_views, total_tiles, o, out_T,
+                                         out_n, out_last, out_idx, out_depth, out_normal, counters,
+                                         selection_zeros(bf16 ? 8 : 4, C, o.topk) ? out_feat : nullptr, C, ws, s);
+    if (e != hipSuccess) return e;
     const bool vec = C % (bf16 ? 8 : 4) == 0;
 #define FS_GATHER_FORM(FT, VE, LABEL)                                                                             \
     launch_gather<FT, VE, LABEL>(ws.topk_pairs, out_n, ws.topk_rows, ws.topk_nrows, feats, C, o.topk, cams,      \

@@ -1,5 +1,5 @@
 """The zero features of blocks that blend nothing are written by the selection up to
-256 channels and by the gather beyond: every element is written (the image starts as
+256 channels (in rows of 16-byte vectors, K <= 16) and by the gather beyond: every element is written (the image starts as
 NaN) and equals the fused render's, on both sides of that line."""
 from __future__ import annotations
 
