@@ -1022,6 +1022,9 @@ hipError_t fs_launch_render_forward(const FsRecord* records, const uint64_t* key
                                     int32_t* out_idx, float* out_depth, float* out_normal, uint64_t* counters,
                                     const FsWorkspace& ws, hipStream_t s);
 
+// Compute units of the current device (256 if the query fails).
+int fs_device_cus();
+
 // Work queues of the persistent render and the spacing of their tickets
 // (256 B apart).  A ticket is a memory-side atomic, serialised per address:
 // one ticket for every item of the frame limited the full blend (0.39 ms,

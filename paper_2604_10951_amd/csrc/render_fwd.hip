@@ -751,16 +751,6 @@ order_place_kernel(const uint32_t* __restrict__ ranges, int sb2, uint32_t nblock
 
 constexpr int64_t kMaxRow = int64_t(1) << 23;   // workgroups of 256 threads in one row of a launch
 
-int device_cus() {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            cus = 256;
-    }
-    return cus;
-}
-
 template <int NVT, typename FT, int NW, int BG, bool EXT, bool FILTER>
 hipError_t launch_wide(const FsRecord* records, const uint64_t* keys, const uint32_t* vals, const uint32_t* ranges,
                        const void* feats, int C, int64_t n, const fs_camera* cams, int num_views, int64_t total_tiles,
@@ -785,7 +775,7 @@ hipError_t launch_wide(const FsRecord* records, const uint64_t* keys, const uint
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), NW * 64, 0) !=
                 hipSuccess || per_cu < 1)
             per_cu = 1;
-        grid = (int64_t)device_cus() * per_cu;
+        grid = (int64_t)fs_device_cus() * per_cu;
     }
     // and with enough lists to order: with fewer surfels than blocks most blocks
     // have none (2,000 surfels, 1280x720, C = 64, tile 16: render 61 us with the
@@ -836,6 +826,17 @@ hipError_t launch_waves(const FsRecord* records, const uint64_t* keys, const uin
 }
 
 }  // namespace
+
+int fs_device_cus() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+            n = 256;
+        return n;
+    }();
+    return cus;
+}
 
 hipError_t fs_launch_block_order(const uint32_t* ranges, int sb2, uint32_t nblocks, const FsWorkspace& ws,
                                  hipStream_t s) {

@@ -40,6 +40,9 @@ constexpr uint32_t kCoopMost = 2560;    // unless there are more of them than th
 constexpr uint32_t kCoopAll = 1024;     // and all long-list blocks if there are no more than that (917 of them:
                                         // 84 us, 95 without; 1,950: 111 with, 107 without)
 constexpr int kZeroVectors = 64;    // widest rows (float32; bfloat16: 32) of blocks whose zeros the selection writes
+constexpr int kSelWaves = 2;    // waves per workgroup (one block each, or one long-list block together): with a
+                                // block per wave, 1280x720 C = 128 frame, Top-K render 0.1887 / 0.1862 / 0.1951 ms
+                                // for one, two and four
 constexpr int kSelGroup = 256;       // blocks per group of the long-block list
 constexpr int kGatherThreads = 256;
 constexpr int kGatherUnroll = 8;  // (surfel, weight) pairs whose row loads are in flight together
@@ -1121,36 +1124,38 @@ hipError_t fs_launch_topk_select(const FsRecord* records, const uint64_t* keys, 
            : (o.topk <= 8 ? topk_select_kernel<8, false, false, WPG>                                            \
                           : (o.topk <= kCompactK ? topk_select_kernel<kCompactK, false, false, WPG>              \
                                                  : topk_select_kernel<0, false, false, WPG>)))
-    // long-list blocks first: their list, then nblocks waves for them and
-    // nblocks for the grid order
+    // (the passes over the lists launch kGatherThreads threads a block, fewer than
+    // 2^32 in all)
     if (ws.sel_long == nullptr || ws.sel_counts == nullptr || nblocks > ws.render_max_blocks ||
-        2 * nblocks >= (int64_t(1) << 31))
+        nblocks * kGatherThreads >= (int64_t(1) << 32))
         return hipErrorInvalidValue;
-    // (a launch holds fewer than 2^32 threads: without the long part beyond that)
+    const auto kern = FS_SEL_KERN(kSelWaves);
+    // long-list blocks first: their list, then workgroups for as many of them as
+    // there can be, then the blocks in grid order
+    const bool by_weight = o.topk_mode == FS_TOPK_WEIGHT;
     const int64_t long_waves = (nblocks + kSelGroup - 1) / kSelGroup * kSelGroup;
-    int64_t long_wgs = long_waves / 2;
-    if (o.topk_mode == FS_TOPK_WEIGHT)   // and up to kCoopMost more for blocks that take a workgroup each
-        long_wgs = long_waves < kCoopMost ? long_waves : long_waves / 2 + kCoopMost / 2;
-    uint32_t nlong = (long_wgs + nblocks / 2 + 1) * 128 < (int64_t(1) << 32) ? (uint32_t)long_wgs : 0u;
-    // first-K frames whose blocks are all in flight at once (sixteen waves on each
-    // of 256 CUs) need no order: without the list launch and the waves that find
-    // no long block a label frame of 2,267 surfels, 223x169, takes 75.8 us
-    // instead of 78.8
-    if (o.topk_mode != FS_TOPK_WEIGHT && nblocks <= 4096) nlong = 0u;
+    uint32_t nlong = (uint32_t)(long_waves / kSelWaves);
+    if (by_weight)   // and up to kCoopMost more for blocks that take a workgroup each
+        nlong = long_waves < kCoopMost ? (uint32_t)long_waves : nlong + kCoopMost / 2;
+    // first-K frames whose blocks are all in flight at once need no order: without
+    // the list launch and the waves that find no long block a label frame of 2,267
+    // surfels, 223x169, takes 75.8 us instead of 78.8
+    const int cus = fs_device_cus();
+    if (!by_weight && nblocks <= 32 * (int64_t)cus) {   // (no more waves fit a CU)
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), 64 * kSelWaves,
+                                                         0) == hipSuccess &&
+            nblocks <= (int64_t)cus * per_cu * kSelWaves)
+            nlong = 0u;
+    }
     if (nlong != 0u)
         hipLaunchKernelGGL(select_long_kernel, dim3((unsigned)((nblocks + kSelGroup - 1) / kSelGroup)), dim3(kSelGroup),
-                           0, s, ranges, sb * sb, nblocks, o.topk_mode == FS_TOPK_WEIGHT ? kSelCoop : ~0u, ws.sel_long,
+                           0, s, ranges, sb * sb, nblocks, by_weight ? kSelCoop : ~0u, ws.sel_long,
                            ws.sel_counts);
-#define FS_SEL_LAUNCH(WPG)                                                                                      \
-    hipLaunchKernelGGL(FS_SEL_KERN(WPG), dim3((unsigned)(nlong + (nblocks + WPG - 1) / WPG)), dim3(64 * WPG), 0, s,   \
-                       records, keys, vals, ranges, (uint32_t)n, n * num_views, cams, num_views, o.tile, o, nblocks,  \
-                       ws.topk_pairs, ws.topk_rows, ws.topk_nrows, out_T, out_n, out_last, out_idx, out_depth,        \
-                       out_normal, counters, ws.sel_long, ws.sel_counts, nlong, out_feat, C)
-    // two selection waves per workgroup (one block each, or one long-list block
-    // together): measured on the 1280x720 C = 128 frame with a block per wave,
-    // Top-K render 0.1887 / 0.1862 / 0.1951 ms for one, two and four waves
-    FS_SEL_LAUNCH(2);
-#undef FS_SEL_LAUNCH
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nlong + (nblocks + kSelWaves - 1) / kSelWaves)), dim3(64 * kSelWaves), 0, s,
+                       records, keys, vals, ranges, (uint32_t)n, n * num_views, cams, num_views, o.tile, o, nblocks,
+                       ws.topk_pairs, ws.topk_rows, ws.topk_nrows, out_T, out_n, out_last, out_idx, out_depth,
+                       out_normal, counters, ws.sel_long, ws.sel_counts, nlong, out_feat, C);
 #undef FS_SEL_KERN
     return hipGetLastError();
 }
