@@ -39,7 +39,6 @@ constexpr uint32_t kCoopMost = 2560;    // unless there are more of them than th
                                         // 535 without; 3,480: 522 with, 472 without),
 constexpr uint32_t kCoopAll = 1024;     // and all long-list blocks if there are no more than that (917 of them:
                                         // 84 us, 95 without; 1,950: 111 with, 107 without)
-constexpr int kZeroVectors = 64;    // widest rows (float32; bfloat16: 32) of blocks whose zeros the selection writes
 constexpr int kSelWaves = 2;    // waves per workgroup (one block each, or one long-list block together): with a
                                 // block per wave, 1280x720 C = 128 frame, Top-K render 0.1887 / 0.1862 / 0.1951 ms
                                 // for one, two and four
@@ -173,6 +172,13 @@ FS_DEV int64_t select_block_of(int64_t nblocks, uint32_t nlong, const fs_camera*
     }
     return -1;   // fewer long blocks than i + 1
 }
+
+// Whether the selection writes the zero features of the blocks without rows, for the
+// staged gather's rows of nv vectors of ve elements: up to 8 the gather's stores cost
+// less (20k surfels, 1280x720, C = 16: render 53.4 us, 52.4 by the gather), and the
+// widest hold a selection wave up for too long (200k, 1280x720, bfloat16, C = 512:
+// 570, 557; C = 256 313, 323; float32 C = 128 140, 161).
+constexpr bool selection_zeros(int ve, int nv) { return nv > 8 && nv * ve <= 256; }
 
 // One wave writes the zero features of an 8x8 block (the part inside the
 // image), row by row: a pixel row's channels are contiguous.  Non-temporal, as
@@ -678,10 +684,7 @@ topk_select_kernel(const FsRecord* __restrict__ records, const uint64_t* __restr
     // a block that blends nothing gets its zero features here and the gather
     // skips it: the walks leave the memory idle, and two thirds of the
     // 1M-surfel 1280x720 C = 128 image are such blocks (select + gather
-    // 60 + 127 us without, 86 + 80 us with; frame 375 -> 355 us.  Wider images hold
-    // a selection wave up for too long: 50k surfels, 640x480, C = 256 96 -> 86 us, but
-    // C = 320 170 -> 179 and C = 1024 282 -> 321; 200k, 1280x720, bfloat16 C = 256
-    // 323 -> 313, but C = 512 556 -> 570)
+    // 60 + 127 us without, 86 + 80 us with; frame 375 -> 355 us)
     if (out_feat != nullptr && nslots == 0u) zero_block(out_feat, C, cam, bp);
     if (inside) {
         if (out_T) out_T[pix] = (float)T;
@@ -930,7 +933,7 @@ topk_gather_lds_kernel(const uint2* __restrict__ pairs, const int32_t* __restric
     for (int v = 0; v < NVT; ++v) has_vec[v] = q + v * TPP < nv;
     const uint32_t nr = nrows[block];
     const uint32_t R = nr & 0xffffu, NP = nr >> 16;   // rows and listed pairs of the block
-    if (!LABEL && 4 * TPP * NVT <= kZeroVectors * (int)sizeof(FT) && R == 0u) return;   // the selection wrote its zeros
+    if (!LABEL && selection_zeros(VE, TPP * NVT) && R == 0u) return;   // the selection wrote its zeros
     const uint32_t* __restrict__ rowlist = rows + block * 64 * (int64_t)K;
     // lists, counts and the row list: one round trip
     if (R > 0)
@@ -1035,10 +1038,8 @@ topk_gather_lds_kernel(const uint2* __restrict__ pairs, const int32_t* __restric
     }
 }
 
-// Whether the staged gather takes a render, and whether the selection writes the
-// zero features of its blocks without rows (the general gather writes its own).
+// Whether the staged gather takes a render (rows of ve-element vectors).
 bool staged_gather(int ve, int C, int K) { return C % ve == 0 && C / ve <= 64 && K <= kStagedK; }
-bool selection_zeros(int ve, int C, int K) { return staged_gather(ve, C, K) && (ve == 4 || C / ve <= 32); }
 
 template <typename FT, int VE, bool LABEL>
 hipError_t launch_gather(const uint2* pairs, const int32_t* counts, const uint32_t* rows, const uint32_t* nrows,
@@ -1175,9 +1176,14 @@ hipError_t fs_launch_render_topk_split(const FsRecord* records, const uint64_t* 
         (out_feat == nullptr) == (out_label == nullptr))
         return hipErrorInvalidValue;
     const bool bf16 = o.feat_dtype == FS_FEAT_BF16;
+    // the gather's kernel is chosen by the vectors of a row, and takes the zeros as
+    // written or not by the widest row it is made for
+    const int ve = bf16 ? 8 : 4, nv = C / ve;
+    const int widest = nv <= 4 ? 4 : nv <= 8 ? 8 : nv <= 16 ? 16 : nv <= 32 ? 32 : 64;
+    const bool by_select = staged_gather(ve, C, o.topk) && selection_zeros(ve, widest);
     hipError_t e = fs_launch_topk_select(records, keys, vals, ranges, n, cams, num_views, total_tiles, o, out_T,
                                          out_n, out_last, out_idx, out_depth, out_normal, counters,
-                                         selection_zeros(bf16 ? 8 : 4, C, o.topk) ? out_feat : nullptr, C, ws, s);
+                                         by_select ? out_feat : nullptr, C, ws, s);
     if (e != hipSuccess) return e;
     const bool vec = C % (bf16 ? 8 : 4) == 0;
 #define FS_GATHER_FORM(FT, VE, LABEL)                                                                             \

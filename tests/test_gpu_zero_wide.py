@@ -1,5 +1,5 @@
 """The zero features of blocks that blend nothing are written by the selection up to
-256 channels (in rows of 16-byte vectors, K <= 16) and by the gather beyond: every element is written (the image starts as
+256 channels (in rows of more than 8 vectors, K <= 16) and by the gather otherwise: every element is written (the image starts as
 NaN) and equals the fused render's, on both sides of that line."""
 from __future__ import annotations
 
@@ -11,8 +11,9 @@ from paper_2604_10951_amd import raster, scenes
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("C,K,dtype", [(256, 8, "f32"), (257, 8, "f32"), (260, 16, "f32"), (260, 20, "f32"),
-                                       (1024, 3, "f32"), (256, 8, "bf16"), (264, 8, "bf16"), (520, 16, "bf16")])
+@pytest.mark.parametrize("C,K,dtype", [
+    (32, 8, "f32"), (36, 8, "f32"), (64, 16, "bf16"), (72, 16, "bf16"), (256, 8, "f32"), (257, 8, "f32"),
+    (260, 16, "f32"), (260, 20, "f32"), (1024, 3, "f32"), (256, 8, "bf16"), (264, 8, "bf16"), (520, 16, "bf16")])
 def test_wide_images(C, K, dtype):
     print(f"[case] zero blocks, wide C={C} K={K} {dtype}", flush=True)
     scene = scenes.uniform_scene(60, seed=4, scale_range=(0.01, 0.04), feat_channels=C - 3)
