@@ -38,7 +38,11 @@ struct __align__(16) FsRecord {
     double k2;                  // cutoff k^2 (-1: culled)
     float o;                    // opacity
     int16_t ax, ay;             // anchor pixel (view-local)
-    int16_t x0, x1, y0, y1;     // pixel bounding box of the footprint, clamped (x0 > x1: empty)
+    // Pixel bounding box of the footprint, clamped (x0 > x1: empty).  It holds
+    // every pixel centre inside the exact footprint conic; outside it the d2 test
+    // can only pass by rounding, so every renderer evaluates and accepts pixels
+    // inside the box only, and their decisions agree.
+    int16_t x0, x1, y0, y1;
 };
 static_assert(sizeof(FsRecord) == FS_RECORD_BYTES, "record size");
 
@@ -785,17 +789,6 @@ FS_DEV float3 fs_record_normal(const FsRecord& r, const fs_camera& cam) {
     return make_float3((float)(m0 * inv), (float)(m1 * inv), (float)(m2 * inv));
 }
 
-// A pixel is accepted only inside the record's pixel box (it holds every
-// pixel centre inside the exact footprint conic; outside it the d2 test can
-// only pass by rounding).  Every renderer applies the same test, so their
-// accept decisions agree wherever they evaluate a pixel.
-FS_DEV bool fs_in_box(const FsRecord& r, int px, int py) {
-    return (px >= r.x0) & (px <= r.x1) & (py >= r.y0) & (py <= r.y1);
-}
-
-// Record index -> surfel index for record r = v * n + i.
-FS_DEV int64_t fs_surfel_of(int64_t rec, int64_t n) { return rec % n; }
-
 // View of a global tile id (binary search over tile offsets; num_views is small).
 FS_DEV int fs_view_of_tile(const fs_camera* cams, int num_views, int64_t tile) {
     int lo = 0, hi = num_views - 1;
@@ -868,11 +861,6 @@ FS_DEV int64_t block_row_chunk(const fs_camera* cams, int S) {
     return tiles_x * sb * sb;
 }
 
-// Bitonic sort of 64 << LOGE keys by one wave, in registers: element
-// i = lane * 2^LOGE + e is x[e] of its lane.  Compare-exchange partners
-// i ^ j with j < 2^LOGE sit in the same lane; with larger j they are the
-// same register of lane ^ (j >> LOGE), fetched by a shuffle.  The network is
-// the textbook one (stage k, distance j, ascending where i & k == 0).
 // Wave-wide inclusive prefix sums and reductions of the ROCm device library:
 // lane shifts and row broadcasts in registers, with no LDS round trip (a
 // chain of six shuffles costs six).  Every lane of the wave must be active.
@@ -915,6 +903,11 @@ FS_DEV uint64_t lane_xor64(uint64_t v, int lm) {
     return (uint64_t)hi << 32 | lo;
 }
 
+// Bitonic sort of 64 << LOGE keys by one wave, in registers: element
+// i = lane * 2^LOGE + e is x[e] of its lane.  Compare-exchange partners
+// i ^ j with j < 2^LOGE sit in the same lane; with larger j they are the
+// same register of lane ^ (j >> LOGE), fetched by a shuffle.  The network is
+// the textbook one (stage k, distance j, ascending where i & k == 0).
 template <int LOGE>
 FS_DEV void wave_network(uint64_t (&x)[1 << LOGE]) {
     constexpr int E = 1 << LOGE;
