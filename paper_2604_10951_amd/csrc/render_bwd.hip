@@ -94,7 +94,8 @@ constexpr int kBwdThreads = 256;
 constexpr int kBwdGroup = 16;
 constexpr int kBwdGroups = kBwdThreads / kBwdGroup;
 constexpr int kBwdQueue = 512;   // entries queued by the filter (a power of two)
-constexpr uint32_t kBwdLong = 64;   // blocks with longer lists are started first
+constexpr uint32_t kBwdLong = 64;   // blocks with longer lists are started first (200k surfels, 640x480, C = 48,
+                                    // 8x8 tiles: 225 us, 245 from 16 and 248 from 256 entries, 260 without)
 
 // FILTER (tiles larger than a block): only entries whose pixel boxes meet the
 // block are walked, queued 256 list positions at a time.
