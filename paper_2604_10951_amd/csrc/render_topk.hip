@@ -817,8 +817,7 @@ constexpr int kNoChannel = 0x7fffffff;
 template <typename FT, int VE, int TPP, bool LABEL>
 __global__ void __launch_bounds__(kGatherThreads)
 topk_gather_general_kernel(const uint2* __restrict__ pairs, const int32_t* __restrict__ counts,
-                           const uint32_t* __restrict__ rows, const uint32_t* __restrict__ nrows,
-                           const FT* __restrict__ feats, int C, int K,
+                           const uint32_t* __restrict__ rows, const FT* __restrict__ feats, int C, int K,
                            const fs_camera* __restrict__ cams, int num_views, int S, int64_t ngroups,
                            float* __restrict__ out_feat, int32_t* __restrict__ out_label,
                            float* __restrict__ out_score) {
@@ -1088,7 +1087,7 @@ hipError_t launch_gather(const uint2* pairs, const int32_t* counts, const uint32
     if (groups >= (int64_t(1) << 32)) return hipErrorInvalidValue;
 #define FS_GATHER(TPP)                                                                                            \
     hipLaunchKernelGGL((topk_gather_general_kernel<FT, VE, TPP, LABEL>), dim3((unsigned)groups),                   \
-                       dim3(kGatherThreads), 0, s, pairs, counts, rows, nrows, f, C, K, cams, num_views, S, groups,  \
+                       dim3(kGatherThreads), 0, s, pairs, counts, rows, f, C, K, cams, num_views, S, groups,  \
                        out_feat, \
                        out_label, out_score)
     switch (tpp) {
